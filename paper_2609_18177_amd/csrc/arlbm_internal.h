@@ -17,6 +17,20 @@ constexpr int kOutW = kWave - 2 * kHalo;  // 58
 __host__ __device__ constexpr int strip_halo(int v) { return (kHalo + v - 1) / v * v; }
 __host__ __device__ constexpr int strip_out_w(int v) { return kWave * v - 2 * strip_halo(v); }
 static_assert(strip_out_w(1) == kOutW && strip_out_w(2) == 120, "strip geometry");
+// The one-workgroup march of a small 1D lattice: at most kMarchWaves waves, of
+// one cell per lane where 58 cells a wave hold the lattice, else of two (one
+// cell per lane is the faster wherever both hold it: Euler FP32 400 cells 1.67
+// against 1.70 us per step, 100 cells 1.08 against 1.51).  Two cells per lane
+// beat one launch per step (4.1-4.7 us) for advection and for FP32 Euler and
+// shallow water (at 1920 cells 1.13-1.73, 3.95 and 3.14 us); FP64 Euler and
+// shallow water (6.2 and 5.7 against 5.3 us) and the reactive system (7.3
+// against 5.8, 17.5 against 7.3) lose, so they march up to 928 cells.
+constexpr int kMarchWaves = 16;
+__host__ __device__ constexpr int march_width(int64_t nx) { return nx <= kMarchWaves * strip_out_w(1) ? 1 : 2; }
+constexpr int march_cells(int system, bool f64)
+{
+    return kMarchWaves * strip_out_w(system == 0 || (!f64 && system != 3) ? 2 : 1);
+}
 constexpr int kBlock = 256;               // 4 independent waves per block
 constexpr int kWavesPerBlock = kBlock / kWave;
 

@@ -144,18 +144,28 @@ hipError_t step_single(const LatticeDesc &h, int64_t iter, hipStream_t s)
 #undef C_
 }
 
+template <int SYS>
+static hipError_t march_impl(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
+{
+    if (h.nx > march_cells(SYS, sizeof(real) == 8)) return hipErrorInvalidValue;
+    const int v = march_width(h.nx), ow = strip_out_w(v), nw = (h.nx + ow - 1) / ow;
+    constexpr int kTwo = march_cells(SYS, sizeof(real) == 8) > kMarchWaves * strip_out_w(1) ? 2 : 1;
+    if (v == 2)
+        hipLaunchKernelGGL((k_march1d<SYS, real, kTwo>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
+    else
+        hipLaunchKernelGGL((k_march1d<SYS, real, 1>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
+    return hipGetLastError();
+}
+
 hipError_t steps1d(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
 {
-    const int nw = h.ncols < 16 ? h.ncols : 16;  // one wave per strip up to 16
-    const dim3 g(1), b(64 * nw);
     switch (h.variant) {
-    case V_ADV1: hipLaunchKernelGGL((k_steps1d<0, real>), g, b, 0, s, h, iter0, nsteps); break;
-    case V_EUL1: hipLaunchKernelGGL((k_steps1d<1, real>), g, b, 0, s, h, iter0, nsteps); break;
-    case V_SWE1: hipLaunchKernelGGL((k_steps1d<2, real>), g, b, 0, s, h, iter0, nsteps); break;
-    case V_REU1: hipLaunchKernelGGL((k_steps1d<3, real>), g, b, 0, s, h, iter0, nsteps); break;
+    case V_ADV1: return march_impl<0>(h, iter0, nsteps, s);
+    case V_EUL1: return march_impl<1>(h, iter0, nsteps, s);
+    case V_SWE1: return march_impl<2>(h, iter0, nsteps, s);
+    case V_REU1: return march_impl<3>(h, iter0, nsteps, s);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t step_batched(const LatticeDesc *d_descs, const Segment *d_segs, const int32_t *d_qstart,

@@ -691,31 +691,32 @@ extern "C" int arlbm_set_state_device(arlbm_lattice *h, const double *U0, const 
     return set_state_impl(h, U0, bed, true, t0);
 }
 
-constexpr int32_t kSteps1dMaxStrips = 16, kSteps1dRun = 1024;
+// Enqueue n steps.  A small 1D lattice takes them in launches of up to
+// kMarchRun steps of one workgroup (k_march1d), the same bits as one launch
+// per step.
+constexpr int32_t kMarchRun = 1024;
+static hipError_t enqueue_steps(arlbm_lattice *h, int64_t n)
+{
+    const bool march = h->cfg.dim == 1 && n >= 2 && h->cfg.nx <= march_cells(h->cfg.system, is_f64(h));
+    while (n > 0) {
+        const int32_t k = march ? (int32_t)std::min<int64_t>(n, kMarchRun) : 1;
+        hipError_t e = !march ? L_step(h, h->step)
+                              : (is_f64(h) ? f64::steps1d(h->desc, h->step, k, h->stream)
+                                           : f32::steps1d(h->desc, h->step, k, h->stream));
+        if (e != hipSuccess) return e;
+        h->step += k;
+        n -= k;
+    }
+    return hipSuccess;
+}
 
 extern "C" int arlbm_step(arlbm_lattice *h, int64_t n)
 {
     if (!h) return fail(nullptr, ARLBM_EINVAL, "handle is NULL");
     if (h->busy) return fail(h, ARLBM_EBUSY, "lattice is owned by a server");
     if (n < 0) return fail(h, ARLBM_EINVAL, "n must be >= 0");
-    // a small 1D lattice takes its steps in launches of up to kSteps1dRun
-    // steps of one workgroup (k_steps1d), the same bits as one launch per step
-    if (h->cfg.dim == 1 && h->desc.ncols <= kSteps1dMaxStrips && n >= 2) {
-        while (n > 0) {
-            const int32_t k = (int32_t)std::min<int64_t>(n, kSteps1dRun);
-            hipError_t e = is_f64(h) ? f64::steps1d(h->desc, h->step, k, h->stream)
-                                     : f32::steps1d(h->desc, h->step, k, h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "step launch");
-            h->step += k;
-            n -= k;
-        }
-        return ARLBM_OK;
-    }
-    for (int64_t i = 0; i < n; ++i) {
-        hipError_t e = L_step(h, h->step);
-        if (e != hipSuccess) return hip_fail(h, e, "step launch");
-        ++h->step;
-    }
+    const hipError_t e = enqueue_steps(h, n);
+    if (e != hipSuccess) return hip_fail(h, e, "step launch");
     return ARLBM_OK;
 }
 
@@ -741,13 +742,10 @@ extern "C" int arlbm_step_until(arlbm_lattice *h, double t_final, int64_t max_st
         const double est = sc.last_dt > 0.0 ? (t_final - t) / sc.last_dt : 1.0;
         int64_t k = est < 1e15 ? (int64_t)std::ceil(est) + 1 : 1;
         if (k > max_steps - real) k = max_steps - real;
-        for (int64_t i = 0; i < k; ++i) {
-            hipError_t e = L_step(h, h->step);
-            if (e != hipSuccess) {
-                h->desc.t_stop = HUGE_VAL;
-                return hip_fail(h, e, "step launch");
-            }
-            ++h->step;
+        const hipError_t e = enqueue_steps(h, k);
+        if (e != hipSuccess) {
+            h->desc.t_stop = HUGE_VAL;
+            return hip_fail(h, e, "step launch");
         }
         rc = read_scalars(h, &sc);
         if (rc) break;

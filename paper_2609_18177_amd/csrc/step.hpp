@@ -201,16 +201,12 @@ __device__ __forceinline__ int abar_copy(const LatticeDesc &L)
     return (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & abar_mask(L));
 }
 
+// A step is defined when the sum of the bounds is positive and not absurd.
+__device__ __forceinline__ bool bounds_ok(double sa) { return sa > 0.0 && sa < 1.0e300; }
 template <int D, typename T>
-__device__ __forceinline__ bool step_coefs(const LatticeDesc &L, int64_t n, Coefs<T> &cf)
+__device__ __forceinline__ void coefs_of(const LatticeDesc &L, double ab0, double ab1, double ab2, Coefs<T> &cf)
 {
-    const DevScalars *sc = L.sc;
-    const int slot = (int)(n % 3);
-    const double ab0 = abar_of(L, slot, 0);
-    const double ab1 = D >= 2 ? abar_of(L, slot, 1) : 0.0;
-    const double ab2 = D == 3 ? abar_of(L, slot, 2) : 0.0;
     const double sa = D == 3 ? (ab0 + ab1) + ab2 : (D == 2 ? ab0 + ab1 : ab0);
-    if (!(sa > 0.0) || !(sa < 1.0e300)) return false;
     const double dt = L.cfl * L.dx / sa;
     const double lam = L.dx / dt;
     const double al0 = ab0 + L.eps, al1 = ab1 + L.eps, al2 = ab2 + L.eps;
@@ -224,6 +220,16 @@ __device__ __forceinline__ bool step_coefs(const LatticeDesc &L, int64_t n, Coef
     cf.hdt = T(0.5 * dt);
     cf.omega_fixed = T(L.omega_fixed);
     cf.dt = dt;
+}
+template <int D, typename T>
+__device__ __forceinline__ bool step_coefs(const LatticeDesc &L, int64_t n, Coefs<T> &cf)
+{
+    const int slot = (int)(n % 3);
+    const double ab0 = abar_of(L, slot, 0);
+    const double ab1 = D >= 2 ? abar_of(L, slot, 1) : 0.0;
+    const double ab2 = D == 3 ? abar_of(L, slot, 2) : 0.0;
+    if (!bounds_ok(D == 3 ? (ab0 + ab1) + ab2 : (D == 2 ? ab0 + ab1 : ab0))) return false;
+    coefs_of<D, T>(L, ab0, ab1, ab2, cf);
     return true;
 }
 
@@ -525,28 +531,339 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
     commit<T>(L, n, s0, T(0), flags, 1);
 }
 
-// Several steps of a small 1D lattice in one launch: one workgroup, one wave
-// per strip (at most 16 strips), a barrier between steps.  Before it every
-// wave waits for its stores and wave-speed atomics to complete.  The
-// barrier's workgroup-scope fences then make them visible to the other waves:
-// the waves of one workgroup run on one CU and share its L1, which the CU
-// keeps coherent with its own stores and atomics, so the next step reads the
-// populations, times and slots the step wrote without dropping any cache
-// lines.  A step then costs no launch: a 256-cell advection solve of 512
-// steps took 2.23 ms in one launch per step, 1.52 ms here with an acquire at
-// device scope after the barrier (which invalidates the L1), 1.33 ms without;
-// 900 cells of Euler over 1500 steps 9.07 -> 6.73 ms.  With several strips
-// per wave the strips follow one another: 4096 cells (71 strips on 16 waves)
-// took 25 ms against 9.8 ms, so larger lattices keep one launch per step.
-template <int SYS, typename T>
-__global__ __launch_bounds__(1024) void k_steps1d(LatticeDesc L, int64_t iter0, int32_t nsteps)
+// Many steps of a small 1D lattice in one launch of one workgroup, the state
+// held in registers from the first step to the last.  The cells are dealt
+// evenly to the waves, a wave's cells to its lanes (V adjacent cells per lane)
+// between halo lanes; per step a wave publishes its three outer cells on each
+// side (populations and the primitives the indicator and the flux read) and
+// its wave-speed bound in LDS, and after the step's one barrier reads its
+// halo's cells and every wave's bound.  Two LDS sets in turn: a set is
+// rewritten two steps later, after the barrier that every reader has passed.
+// Nothing else leaves the registers: the populations, the time and the bounds
+// go to memory once, after the last step, as one launch per step leaves them.
+// Lanes outside the lattice's halo hold the nearest halo cell, so that no
+// lane ever computes on an undefined state.
+// What bounds a step: the dependent chain of one wave (LDS read, bound
+// reduction, FP64 time step, indicator, collision, LDS write, barrier) while
+// every SIMD has one wave (up to 232 cells), one CU's instruction issue above.
+// us per step, against the march that kept its populations in memory between
+// steps, and (above 928 cells) one launch per step: advection FP64 256 cells
+// 2.38 -> 0.78, Euler FP32 928 4.45 -> 2.66, FP64 6.61 -> 3.86, shallow water
+// FP64 600 4.81 -> 2.82, reactive FP64 256 7.84 -> 5.36; two cells per lane at
+// 1920 cells: advection FP32 4.06 -> 1.13, Euler FP32 4.41 -> 3.95.
+template <int SYS>
+__host__ __device__ constexpr int march_values()
 {
-    const int nw = (int)(blockDim.x >> 6), w = (int)(threadIdx.x >> 6);
-    const int c0 = (int)((int64_t)w * L.ncols / nw), c1 = (int)((int64_t)(w + 1) * L.ncols / nw);
-    for (int s = 0; s < nsteps; ++s) {
-        if (c0 < c1) seg1d<SYS, T>(L, iter0 + s, c0, c1);
-        __builtin_amdgcn_s_waitcnt(0);  // vmcnt, expcnt and lgkmcnt all zero
+    return 3 * SysInfo<SYS, 1>::M + (SYS == 0 ? 0 : (SYS == 3 ? 4 : 3));
+}
+template <int SYS, typename T, int V>
+__global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, int64_t iter0, int32_t nsteps)
+{
+    constexpr int D = 1, M = SysInfo<SYS, 1>::M, Q = 3, NV = march_values<SYS>(), HC = strip_halo(V);
+    __shared__ T edge[2][kMarchWaves][2 * kHalo][NV];
+    __shared__ T bound[2][kMarchWaves];
+    const int lane = (int)(threadIdx.x & (kWave - 1)), wave = (int)(threadIdx.x >> 6);
+    const int nw = (int)(blockDim.x >> 6), nx = L.nx;
+    auto first_cell = [&](int w) { return (int)((int64_t)w * nx / nw); };
+    const int c0 = first_cell(wave), c1 = first_cell(wave + 1);
+    const int64_t n0 = iter0 - L.iter0;
+    const DevScalars *sc = L.sc;
+    const Phys<T> P = make_phys<T>(L);
+    constexpr bool src = SYS == 2;
+    const bool has_bed = src && L.bed != nullptr;
+    if (threadIdx.x < 2 * kMarchWaves) bound[threadIdx.x & 1][threadIdx.x >> 1] = T(0);
+    __syncthreads();
+
+    int x[V], from[V];  // the lane's cells; the LDS slot a halo cell is read from, -1 for the wave's own cells
+    int to[V];          // the LDS slot an own cell is published in, or -1
+    unsigned xo[V];
+    bool own[V], rx[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        x[v] = c0 - HC + lane * V + v;
+        own[v] = x[v] >= c0 && x[v] < c1;
+        const int xc = x[v] < c0 - kHalo ? c0 - kHalo : (x[v] > c1 - 1 + kHalo ? c1 - 1 + kHalo : x[v]);
+        const int xm = bc_map(xc, nx, L.bc[0], L.bc[1], rx[v]);
+        xo[v] = (unsigned)xm;
+        int ow = (int)(((int64_t)xm * nw) / nx);  // the wave that owns the cell
+        while (first_cell(ow + 1) <= xm) ++ow;
+        const int rel = xm - first_cell(ow), right = first_cell(ow + 1) - kHalo - first_cell(ow);
+        const int k = rel < kHalo ? rel : kHalo + (rel > right ? rel - right : 0);
+        from[v] = own[v] ? -1 : ow * (2 * kHalo) + k;
+        to[v] = own[v] && (rel < kHalo || rel >= right) ? wave * (2 * kHalo) + k : -1;
+    }
+
+    T f[V][Q][M], U[V][M], db[V];
+    Prim<T> q[V];
+    auto moments = [&](int v) __attribute__((always_inline)) {  // (2.3), velocity order, with the ghost map
+#pragma unroll
+        for (int c = 0; c < M; ++c) U[v][c] = f[v][0][c] + f[v][1][c] + f[v][2][c];
+        if constexpr (SYS != 0)
+            if (rx[v]) U[v][1] = -U[v][1];
+    };
+    auto left_of = [&](const T (&a)[V], T (&o)[V]) __attribute__((always_inline)) {
+        o[0] = from_left(a[V - 1]);
+#pragma unroll
+        for (int v = 1; v < V; ++v) o[v] = a[v - 1];
+    };
+    auto right_of = [&](const T (&a)[V], T (&o)[V]) __attribute__((always_inline)) {
+        o[V - 1] = from_right(a[0]);
+#pragma unroll
+        for (int v = 0; v < V - 1; ++v) o[v] = a[v + 1];
+    };
+    {
+        const T *fin = (const T *)L.f[n0 & 1];
+        T b[V], bl[V], br[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+#pragma unroll
+            for (int k = 0; k < Q; ++k)
+#pragma unroll
+                for (int c = 0; c < M; ++c) f[v][k][c] = ldo(fin + (size_t)(k * M + c) * L.pstride, xo[v]);
+            b[v] = has_bed ? ((const T *)L.bed)[xo[v]] : T(0);
+            moments(v);
+            primitives<SYS, D, T>(U[v], P, q[v]);
+        }
+        // bed slope by central differences, the same in every step
+        left_of(b, bl);
+        right_of(b, br);
+#pragma unroll
+        for (int v = 0; v < V; ++v) db[v] = has_bed ? ddiv<T>(br[v] - bl[v], T(2) * P.dx) : T(0);
+    }
+    double t = sc->t[n0 % 3], t_before = t, last_dt = sc->last_dt;
+    double ab = abar_of(L, (int)(n0 % 3), 0);
+    const unsigned long long null0 = sc->null_launches;
+    unsigned flags = 0;
+    unsigned long long bad = ~0ull;
+    Coefs<T> cf0;
+    coefs_of<D, T>(L, ab, 0.0, 0.0, cf0);
+    int32_t s = 0;
+    for (; s < nsteps; ++s) {
+        const int64_t n = n0 + s;
+        if (!bounds_ok(ab)) {
+            flags |= 4u;
+            if (bad == ~0ull) bad = (unsigned long long)n - null0;
+            break;
+        }
+        if (t >= L.t_stop) break;
+        // (formed beside the indicator, which does not need them)
+        Coefs<T> cf;
+        if constexpr (SYS == 0) cf = cf0;  // the bound is the advection speed in every step
+        else coefs_of<D, T>(L, ab, 0.0, 0.0, cf);
+        // neighbours, indicator (2.9)-(2.10), 3-point sum (2.11), omega (2.12)
+        T UL[V][M], UR[V][M], nu[V], nuL[V], nuR[V], w[V];
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            T a[V], l[V], r[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) a[v] = U[v][c];
+            left_of(a, l);
+            right_of(a, r);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                UL[v][c] = l[v];
+                UR[v][c] = r[v];
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            nu[v] = T(0);
+            add_theta<SYS, D, T>(0, q[v], U[v], UL[v], UR[v], P, nu[v]);
+        }
+        left_of(nu, nuL);
+        right_of(nu, nuR);
+        // equilibrium (2.18) and collision at the source nodes
+        T fs[V][Q][M];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const T nt = nuL[v] + nu[v] + nuR[v];
+            w[v] = L.omega_fixed_on ? cf.omega_fixed : omega_of<T>(nt);
+            if (L.omega_on && own[v]) ((T *)L.omega)[x[v]] = w[v];
+            T F[M];
+            flux<SYS, D, T>(0, U[v], q[v], P, F);
+#pragma unroll
+            for (int c = 0; c < M; ++c) {
+                const T u = U[v][c];
+                const T feq0 = cf.a0 * u;
+                const T feq1 = cf.ap[0] * u + cf.bp * F[c];
+                const T feq2 = cf.ap[0] * u + cf.bm * F[c];
+                const T f0 = f[v][0][c], f1 = f[v][1][c], f2 = f[v][2][c];
+                fs[v][0][c] = f0 - w[v] * (f0 - feq0);
+                fs[v][1][c] = f1 - w[v] * (f1 - feq1);
+                fs[v][2][c] = f2 - w[v] * (f2 - feq2);
+            }
+            const T ak[Q] = {cf.a0, cf.ap[0], cf.ap[0]};
+            if constexpr (src) {
+                if (has_bed) {
+                    const T S1 = -P.g * U[v][0] * db[v];
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) fs[v][k][1] = fs[v][k][1] + cf.hdt * (ak[k] * S1);
+                }
+            }
+            if constexpr (SYS == 3) {  // Arrhenius sink of rho Y, first half (2.6)
+                const T SY = -arrhenius_rate<T>(P, U[v][0], reactive_eint<D, T>(U[v]), U[v][M - 1], nullptr);
+#pragma unroll
+                for (int k = 0; k < Q; ++k) fs[v][k][M - 1] = fs[v][k][M - 1] + cf.hdt * (ak[k] * SY);
+            }
+        }
+        // pull streaming with the ghost map at the two walls
+        T Fp[V][M], Fm[V][M];
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+            T a[V], o[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) a[v] = fs[v][1][c];
+            left_of(a, o);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                Fp[v][c] = o[v];
+                a[v] = fs[v][2][c];
+            }
+            right_of(a, o);
+#pragma unroll
+            for (int v = 0; v < V; ++v) Fm[v][c] = o[v];
+        }
+        T s0 = T(0);
+        unsigned fl = 0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (x[v] == 0 && L.bc[0] != 0) {
+#pragma unroll
+                for (int c = 0; c < M; ++c)
+                    Fp[v][c] = L.bc[0] == 1 ? fs[v][1][c] : (c == 1 ? -fs[v][2][c] : fs[v][2][c]);
+            }
+            if (x[v] == nx - 1 && L.bc[1] != 0) {
+#pragma unroll
+                for (int c = 0; c < M; ++c)
+                    Fm[v][c] = L.bc[1] == 1 ? fs[v][2][c] : (c == 1 ? -fs[v][1][c] : fs[v][1][c]);
+            }
+            // moments (2.8) and second half source
+            T sumF[M];
+#pragma unroll
+            for (int c = 0; c < M; ++c) {
+                f[v][0][c] = fs[v][0][c];
+                f[v][1][c] = Fp[v][c];
+                f[v][2][c] = Fm[v][c];
+                sumF[c] = fs[v][0][c] + Fp[v][c] + Fm[v][c];
+            }
+            const T ak[Q] = {cf.a0, cf.ap[0], cf.ap[0]};
+            if constexpr (src) {
+                if (has_bed) {
+                    const T S1 = -P.g * sumF[0] * db[v];
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) f[v][k][1] = f[v][k][1] + cf.hdt * (ak[k] * S1);
+                }
+            }
+            if constexpr (SYS == 3) {
+                const T eint = reactive_eint<D, T>(sumF);
+                const T z = reactive_solve<T>(P, sumF[0], eint, sumF[M - 1], cf.hdt);
+                const T SY = -arrhenius_rate<T>(P, sumF[0], eint, z, nullptr);
+#pragma unroll
+                for (int k = 0; k < Q; ++k) f[v][k][M - 1] = f[v][k][M - 1] + cf.hdt * (ak[k] * SY);
+            }
+#pragma unroll
+            for (int c = 0; c < M; ++c) U[v][c] = f[v][0][c] + f[v][1][c] + f[v][2][c];
+            primitives<SYS, D, T>(U[v], P, q[v]);
+            if (own[v]) {
+#pragma unroll
+                for (int c = 0; c < M; ++c)
+                    if (!finite_val<T>(U[v][c])) fl |= 1u;
+                fl |= q[v].flags;
+                const T sp = max_speed<SYS, T>(0, q[v], P);
+                if (finite_val<T>(sp) && sp > s0) s0 = sp;
+            }
+        }
+        if (bad == ~0ull && __ballot(fl != 0u)) bad = (unsigned long long)n - null0;
+        flags |= fl;
+        t_before = t;
+        t = t + cf.dt;
+        last_dt = cf.dt;
+        // publish, one barrier, read the halo and the bounds of every wave
+        const int set = s & 1;
+        const T m0 = SYS == 0 ? s0 : wave_max<T>(s0);
+        if (lane == (SYS == 0 ? HC / V : 0)) bound[set][wave] = m0;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (to[v] >= 0) {
+                T *e = &edge[set][0][0][0] + to[v] * NV;
+#pragma unroll
+                for (int k = 0; k < Q; ++k)
+#pragma unroll
+                    for (int c = 0; c < M; ++c) e[k * M + c] = f[v][k][c];
+                if constexpr (SYS != 0) {
+                    e[Q * M] = q[v].vel[0];
+                    e[Q * M + 1] = SYS == 2 ? q[v].mom[0] : q[v].p;
+                    e[Q * M + 2] = q[v].cL;
+                    if constexpr (SYS == 3) e[Q * M + 3] = q[v].Y;
+                }
+            }
+        }
         __syncthreads();
+        T m = bound[set][lane & (kMarchWaves - 1)];
+        m = max_step<0x111, 0xf>(m);
+        m = max_step<0x112, 0xf>(m);
+        m = max_step<0x114, 0xf>(m);
+        m = max_step<0x118, 0xf>(m);
+        ab = (double)read_lane(m, kMarchWaves - 1);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (from[v] >= 0) {
+                const T *e = &edge[set][0][0][0] + from[v] * NV;
+#pragma unroll
+                for (int k = 0; k < Q; ++k)
+#pragma unroll
+                    for (int c = 0; c < M; ++c) f[v][k][c] = e[k * M + c];
+                moments(v);
+                if constexpr (SYS != 0) {
+                    q[v].rho = U[v][0];
+                    q[v].vel[0] = rx[v] ? -e[Q * M] : e[Q * M];
+                    q[v].c = q[v].cL = e[Q * M + 2];
+                    if constexpr (SYS == 2) {
+                        q[v].mom[0] = rx[v] ? -e[Q * M + 1] : e[Q * M + 1];
+                    } else {
+                        q[v].mom[0] = U[v][1];
+                        q[v].E = U[v][2];
+                        q[v].p = e[Q * M + 1];
+                    }
+                    if constexpr (SYS == 3) {
+                        q[v].Z = U[v][M - 1];
+                        q[v].Y = e[Q * M + 3];
+                    }
+                }
+            }
+        }
+    }
+    // the state as nsteps launches leave it (the steps not taken leave it unchanged)
+    __syncthreads();
+    const int64_t ne = n0 + nsteps;
+    T *fout = (T *)L.f[ne & 1];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+        if (own[v])
+#pragma unroll
+            for (int k = 0; k < Q; ++k)
+#pragma unroll
+                for (int c = 0; c < M; ++c) sto(fout + (size_t)(k * M + c) * L.pstride, (unsigned)x[v], f[v][k][c]);
+    unsigned any = flags & 4u;
+    if (__ballot((flags & 1u) != 0u)) any |= 1u;
+    if (__ballot((flags & 2u) != 0u)) any |= 2u;
+    DevScalars *so = L.sc;
+    if (any && lane == 0) {
+        atomicOr(&so->flags, any);
+        atomicMin(&so->first_bad_step, bad);
+    }
+    if (wave == 0) {
+        if (lane == 0) {
+            so->t[(ne + 2) % 3] = s == nsteps ? t_before : t;
+            so->t[ne % 3] = t;
+            so->last_dt = last_dt;
+            so->null_launches = null0 + (any & 4u ? 0ull : (unsigned long long)(nsteps - s));
+        }
+        if (lane <= abar_mask(L)) {
+            AbarCopy &cur = so->abar[ne % 3][lane], &nxt = so->abar[(ne + 1) % 3][lane];
+            cur.v[0] = lane == 0 ? dbits(ab) : 0ull;
+            cur.v[1] = cur.v[2] = nxt.v[0] = nxt.v[1] = nxt.v[2] = 0ull;
+        }
     }
 }
 
