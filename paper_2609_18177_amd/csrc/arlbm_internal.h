@@ -31,6 +31,7 @@ constexpr int march_cells(int system, bool f64)
 {
     return kMarchWaves * strip_out_w(system == 0 || (!f64 && system != 3) ? 2 : 1);
 }
+constexpr int kMaxTileRows = 16;          // rows (waves) of a tile of the tiled 2D step
 constexpr int kBlock = 256;               // 4 independent waves per block
 constexpr int kWavesPerBlock = kBlock / kWave;
 
@@ -86,6 +87,7 @@ struct LatticeDesc {
     int32_t omega_fixed_on;
     int32_t band_h;       // rows per strip (2D)
     int32_t ncols;        // strips along x
+    int32_t tile_rows;    // 2D: rows per tile of the tiled step, 0: the marching step
     int64_t iter0;
     double t_stop;        // a launch whose state time is >= t_stop copies f unchanged (null step)
     int64_t plane;        // nx * ny * nz

@@ -5,6 +5,7 @@
 #include "arlbm_internal.h"
 #include "step.hpp"
 #include "step3d.hpp"
+#include "tile2d.hpp"
 
 #include <mutex>
 
@@ -80,6 +81,16 @@ static hipError_t step_impl(const LatticeDesc &h, int64_t iter, hipStream_t s)
         const int nt = k3_tiles(h.nx, h.ny, G::TX, G::TY);
         const int nb = nt * k3_chunks(nt, h.nz, num_cus());
         hipLaunchKernelGGL((k3_step<SYS, real>), dim3(nb), dim3(G::kThreads), 0, s, h, iter);
+    } else if (D == 2 && h.tile_rows > 0) {
+        const int rows = h.tile_rows, nty = (h.ny + rows - 2 * kHalo - 1) / (rows - 2 * kHalo);
+        const int ncols = (h.nx + kOutW - 1) / kOutW, nwork = ncols * nty;
+        constexpr bool kBed = SYS == 2;
+        if (kBed && h.bed)
+            hipLaunchKernelGGL((k_tile2d<SYS, kBed, real>), dim3(grid_for(nwork, 1)), dim3(kWave * rows),
+                               (tile2d_lds<SYS, kBed, real>(rows)), s, h, iter, nty, nwork);
+        else
+            hipLaunchKernelGGL((k_tile2d<SYS, false, real>), dim3(grid_for(nwork, 1)), dim3(kWave * rows),
+                               (tile2d_lds<SYS, false, real>(rows)), s, h, iter, nty, nwork);
     } else {
         const int64_t nbands = D == 2 ? (h.ny + h.band_h - 1) / h.band_h : 1;
         const int64_t nwork = (int64_t)h.ncols * nbands;

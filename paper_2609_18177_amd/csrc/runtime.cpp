@@ -183,6 +183,36 @@ int num_cus()
     return cus;
 }
 
+// Rows per tile of the tiled 2D step (tile2d.hpp), or 0 where the marching
+// step is the faster.  A tile of r rows writes r - 6 rows of 58 columns, and
+// the tiles are dealt to the CUs one by one, so a CU runs about
+// r * ceil(tiles / CUs) waves; the step's time grows with that number and
+// little else (Euler FP32, us: 48^2 in 8 / 12 / 16 rows 6.3 / 7.1 / 8.0, one
+// tile per CU; 256^2 in 8 / 10 / 12 / 16 rows, 24 / 20 / 12 / 16 waves, 10.3 /
+// 9.6 / 9.1 / 10.2).  The marching step takes the same time for every lattice
+// of bands at its 8-row minimum, up to about 700^2, so there is one line: up
+// to 40 waves per CU the tiles win (512^2, 32 waves, tiles against march:
+// advection FP32 9.2 against 11.5, Euler 19.7 against 21.8, FP64 31.4 against
+// 37.3, reactive FP64 47 against 64), at 64 (700^2) the march (13.5 against
+// 12.2, 35.6 against 24.3, 61 against 41, 93 against 71), but for shallow
+// water, whose march of two columns per lane is the slower (29.4 against 29.5,
+// FP64 50.6 against 55.9).
+int32_t choose_tile_rows(const arlbm_config *c, int64_t cus)
+{
+    const int64_t ncols = (c->nx + kOutW - 1) / kOutW;
+    int32_t best = 0;
+    int64_t best_waves = c->system == ARLBM_SWE ? 64 : 40;
+    for (int32_t rows = kMaxTileRows; rows >= 8; --rows) {
+        const int64_t out = rows - 2 * kHalo, tiles = ncols * ((c->ny + out - 1) / out);
+        const int64_t waves = rows * ((tiles + cus - 1) / cus);
+        if (waves <= best_waves) {
+            best = rows;
+            best_waves = waves;
+        }
+    }
+    return best;
+}
+
 int64_t resident_waves(int precision, int variant, int cpl)
 {
     const int64_t cus = num_cus();
@@ -620,6 +650,7 @@ extern "C" int arlbm_create(const arlbm_config *cfg, const arlbm_buffers *bufs, 
     d.band_h = cfg->dim == 2 ? choose_band(cfg->ny, d.ncols, resident_waves(cfg->precision, d.variant, d.cpl),
                                            4 * (int64_t)num_cus())
                              : 1;
+    d.tile_rows = cfg->dim == 2 ? choose_tile_rows(cfg, num_cus()) : 0;
     d.iter0 = 0;
     d.t_stop = HUGE_VAL;
     d.plane = cfg->nx * cfg->ny * cfg->nz;

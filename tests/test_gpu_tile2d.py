@@ -1,0 +1,41 @@
+"""The tiled 2D step of small lattices (one wave per row of a tile) against the
+oracle and against the batched server's marching strips: FP64 bit for bit (the
+reactive system within the pointwise bound of its two independent root
+finders), FP32 the same bits as the served lattice.  Sizes at the edges of the
+tiles: fewer cells than a halo is wide, one column or row more than a tile's,
+several tiles with ragged ends."""
+import numpy as np
+import pytest
+
+from paper_2609_18177_amd import arlbm as A
+from paper_2609_18177_amd import workloads as W
+from gpu_common import fp64_parity_ok, gpu_lattice, oracle_run, require_gpu, say
+from test_gpu_strips import _served, crop
+
+pytestmark = pytest.mark.gpu
+
+T, R, P = A.TRANSMISSIVE, A.REFLECTIVE, A.PERIODIC
+MAKE = {"advection": lambda: W.advection_sine_2d(n=256, ax=0.8, ay=-0.5), "euler": lambda: W.euler_seeded_2d(4, n=256),
+        "swe": lambda: W.swe_bed_2d(1, n=256), "reactive": lambda: W.reactive_seeded_2d(1, n=256)}
+
+
+@pytest.mark.parametrize("nx,ny", [(4, 4), (58, 6), (59, 7), (116, 10), (117, 33), (200, 101), (250, 256)])
+@pytest.mark.parametrize("system,bc", [("advection", (P,) * 4), ("advection", (T, T, P, P)), ("euler", (T,) * 4),
+                                       ("euler", (R, T, P, P)), ("swe", (R,) * 4), ("swe", (P, P, T, R)),
+                                       ("reactive", (T, R, R, T))])
+def test_tiles_against_oracle_and_served(system, bc, nx, ny):
+    require_gpu()
+    p = crop(MAKE[system](), nx, ny, bc=bc, ox=(256 - nx) // 2, oy=(256 - ny) // 2, steps=12)
+    say(f"[tiles {system} {nx}x{ny} bc={bc}]")
+    Lo = oracle_run(p, p.steps)
+    G = gpu_lattice(p, A.F64, omega_export=True)
+    G.step(p.steps)
+    st = G.sync(check=False)
+    assert fp64_parity_ok(G.moments(), Lo.moments(), p.system)
+    if p.system != A.REACTIVE:
+        assert st["t"] == Lo.t and np.array_equal(G.omega(), Lo.last_omega())
+    G.close()
+    G = gpu_lattice(p, A.F32)
+    G.step(p.steps)
+    assert np.array_equal(G.moments(), _served(p, p.steps))
+    G.close()
