@@ -122,11 +122,26 @@ __host__ __device__ inline int k3_tiles(int nx, int ny, int tx, int ty)
 {
     return ((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
 }
+// The plane chunks of ntiles tiles: the workgroups run in rounds of one per
+// CU, a round as long as its chunks' planes and about 7 more (prologue and the
+// planes around the chunk); the fewest chunks of the least rounds x length.
+// Enough chunks for every CU instead, 160^3 (50 tiles) ran 300 workgroups and
+// 96^3 reactive (36) 288, a second round of a few: Euler FP32 490 -> 321 us,
+// FP64 1222 -> 730, reactive 848 -> 561 and 214 -> 133.
 __host__ __device__ inline int k3_chunks(int ntiles, int nz, int num_cus)
 {
-    const int c = (num_cus + ntiles - 1) / ntiles;
     const int cmax = nz / 8 > 1 ? nz / 8 : 1;
-    return c < 1 ? 1 : (c > cmax ? cmax : c);
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int c = 1; c <= cmax; ++c) {
+        const int64_t rounds = ((int64_t)ntiles * c + num_cus - 1) / num_cus;
+        const int64_t cost = rounds * ((nz + c - 1) / c + 7);
+        if (cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 // A 3D velocity mirrored through its axis (1 <-> 4, 2 <-> 5, 3 <-> 6).
