@@ -6,6 +6,7 @@
 #include "step.hpp"
 #include "step3d.hpp"
 #include "tile2d.hpp"
+#include "tile3d.hpp"
 
 #include <mutex>
 
@@ -76,10 +77,28 @@ template <int SYS, int D>
 static hipError_t step_impl(const LatticeDesc &h, int64_t iter, hipStream_t s)
 {
     if constexpr (D == 3) {
+        // a small lattice in x-y-z tiles (tile3d.hpp), in the lower ones where
+        // they fit one round of the CUs
+        const int cus = num_cus();
+        auto tiles = [&](int tz) { return (int64_t)((h.nx + 7) / 8) * ((h.ny + 7) / 8) * ((h.nz + tz - 1) / tz); };
+        const int ntx = (h.nx + 7) / 8, nty = (h.ny + 7) / 8;
+        using B = Block3<SYS, real, false>;
+        if (tiles(4) <= cus) {
+            const int nwork = (int)tiles(4);
+            hipLaunchKernelGGL((k_tile3d<SYS, real, true>), dim3(grid_for(nwork, 1)), dim3(B::kThreads), 0, s, h, iter,
+                               ntx, nty, nwork);
+            return hipGetLastError();
+        }
+        if (tiles(B::TZ) <= (int64_t)cus * (SYS == 0 ? kTiles3PerCuAdv : kTiles3PerCu)) {
+            const int nwork = (int)tiles(B::TZ);
+            hipLaunchKernelGGL((k_tile3d<SYS, real, false>), dim3(grid_for(nwork, 1)), dim3(B::kThreads), 0, s, h,
+                               iter, ntx, nty, nwork);
+            return hipGetLastError();
+        }
         // one fused pass: tiles x plane chunks filling the chip once
         using G = Tile3<SYS, real>;
         const int nt = k3_tiles(h.nx, h.ny, G::TX, G::TY);
-        const int nb = nt * k3_chunks(nt, h.nz, num_cus());
+        const int nb = nt * k3_chunks(nt, h.nz, cus);
         hipLaunchKernelGGL((k3_step<SYS, real>), dim3(nb), dim3(G::kThreads), 0, s, h, iter);
     } else if (D == 2 && h.tile_rows > 0) {
         const int rows = h.tile_rows, nty = (h.ny + rows - 2 * kHalo - 1) / (rows - 2 * kHalo);
