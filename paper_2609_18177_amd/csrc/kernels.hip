@@ -104,12 +104,16 @@ static hipError_t step_impl(const LatticeDesc &h, int64_t iter, hipStream_t s)
         const int rows = h.tile_rows, nty = (h.ny + rows - 2 * kHalo - 1) / (rows - 2 * kHalo);
         const int ncols = (h.nx + kOutW - 1) / kOutW, nwork = ncols * nty;
         constexpr bool kBed = SYS == 2;
-        if (kBed && h.bed)
-            hipLaunchKernelGGL((k_tile2d<SYS, kBed, real>), dim3(grid_for(nwork, 1)), dim3(kWave * rows),
-                               (tile2d_lds<SYS, kBed, real>(rows)), s, h, iter, nty, nwork);
-        else
-            hipLaunchKernelGGL((k_tile2d<SYS, false, real>), dim3(grid_for(nwork, 1)), dim3(kWave * rows),
-                               (tile2d_lds<SYS, false, real>(rows)), s, h, iter, nty, nwork);
+        const bool buf = nwork > num_cus();  // more than one tile per CU
+#define ARLBM_T2(BED, BUF)                                                                                      \
+    hipLaunchKernelGGL((k_tile2d<SYS, BED, real, BUF>), dim3(grid_for(nwork, 1)), dim3(kWave * rows),         \
+                       (tile2d_lds<SYS, BED, real>(rows)), s, h, iter, nty, nwork)
+        if (kBed && h.bed) {
+            if (buf) ARLBM_T2(kBed, true); else ARLBM_T2(kBed, false);
+        } else {
+            if (buf) ARLBM_T2(false, true); else ARLBM_T2(false, false);
+        }
+#undef ARLBM_T2
     } else {
         const int64_t nbands = D == 2 ? (h.ny + h.band_h - 1) / h.band_h : 1;
         const int64_t nwork = (int64_t)h.ncols * nbands;

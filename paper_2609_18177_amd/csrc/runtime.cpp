@@ -192,11 +192,11 @@ int num_cus()
 // 9.6 / 9.1 / 10.2).  The marching step takes the same time for every lattice
 // of bands at its 8-row minimum, up to about 700^2, so there is one line: up
 // to 40 waves per CU the tiles win (512^2, 32 waves, tiles against march:
-// advection FP32 9.2 against 11.5, Euler 19.7 against 21.8, FP64 31.4 against
-// 37.3, reactive FP64 47 against 64), at 64 (700^2) the march (13.5 against
-// 12.2, 35.6 against 24.3, 61 against 41, 93 against 71), but for shallow
-// water, whose march of two columns per lane is the slower (29.4 against 29.5,
-// FP64 50.6 against 55.9).
+// advection FP32 9.2 against 11.5, Euler 15.8 against 21.4, FP64 31.6 against
+// 37.1, reactive FP64 44 against 63), at 64 (700^2) the march (13.6 against
+// 12.0, 31 against 24, 63 against 41, 87 against 71), but for shallow water,
+// whose march of two columns per lane is the slower (23.8 against 29.1, FP64
+// 50.3 against 54.7).
 int32_t choose_tile_rows(const arlbm_config *c, int64_t cus)
 {
     const int64_t ncols = (c->nx + kOutW - 1) / kOutW;

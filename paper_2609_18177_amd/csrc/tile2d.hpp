@@ -20,6 +20,11 @@
 // Waves outside a stage's rows leave its issue slots to the others.  Every
 // expression is the marching kernel's, so both give the same bits.
 // f* takes the LDS space of U, which nothing reads after the indicator.
+// BUF: plane addresses through buffer resources take about 73 scalar registers
+// instead of 90, and a CU then holds two tiles of 16 rows (512^2 Euler FP32
+// 19.8 -> 15.9 us, shallow water 16.4 -> 13.5, reactive FP64 45.6 -> 44.5; the
+// same vector registers); with at most one tile per CU 64-bit addresses are
+// the faster (64^2 Euler FP32 6.4 against 6.6 us).
 #pragma once
 
 #include "step.hpp"
@@ -44,7 +49,7 @@ constexpr size_t tile2d_lds(int rows)
     return (size_t)rows * tile2d_row_elems<SYS, BED, T>() * sizeof(T) + sizeof(TileShared<T>);
 }
 
-template <int SYS, bool BED, typename T>
+template <int SYS, bool BED, typename T, bool BUF>
 __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, int64_t iter, int32_t ntiles_y, int32_t nwork)
 {
     constexpr int D = 2, M = SysInfo<SYS, 2>::M, Q = 5;
@@ -72,16 +77,17 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
     bool rx, ry;
     const int xm = bc_map(x, nx, bxl, bxh, rx), ym = bc_map(y, ny, byl, byh, ry);
     const unsigned off = (unsigned)ym * (unsigned)nx + (unsigned)xm;
-    const int64_t ps = L.pstride;
 
+    const PlaneIO<T, 1, BUF> io(L, n);
     T f[Q][M];
-    {
-        const T *fin = (const T *)L.f[n & 1];
 #pragma unroll
-        for (int k = 0; k < Q; ++k)
+    for (int k = 0; k < Q; ++k)
 #pragma unroll
-            for (int c = 0; c < M; ++c) f[k][c] = ldo(fin + (size_t)(k * M + c) * ps, off);
-    }
+        for (int c = 0; c < M; ++c) {
+            T v[1];
+            io.ld(k * M + c, off, v);
+            f[k][c] = v[0];
+        }
     T b = T(0);
     if constexpr (BED) b = ((const T *)L.bed)[off];
     // the coefficients, once per tile, by a wave that has no more to do than its moments
@@ -127,16 +133,22 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
     if (w >= 1 && w < rows - 1) {
         T nu = T(0);
         if (!L.omega_fixed_on) {
-            T UL[M], UR[M], Um[M], Up[M];
+            {
+                T UL[M], UR[M];
+#pragma unroll
+                for (int c = 0; c < M; ++c) {
+                    UL[c] = from_left(U[c]);
+                    UR[c] = from_right(U[c]);
+                }
+                add_theta<SYS, D, T>(0, q, U, UL, UR, P, nu);
+            }
+            T Um[M], Up[M];
             const T *um = lF + (size_t)(w - 1) * M * kWave + lane, *up = lF + (size_t)(w + 1) * M * kWave + lane;
 #pragma unroll
             for (int c = 0; c < M; ++c) {
-                UL[c] = from_left(U[c]);
-                UR[c] = from_right(U[c]);
                 Um[c] = um[c * kWave];
                 Up[c] = up[c * kWave];
             }
-            add_theta<SYS, D, T>(0, q, U, UL, UR, P, nu);
             add_theta<SYS, D, T>(1, q, U, Um, Up, P, nu);
         }
         lnu[w * kWave + lane] = nu;
@@ -245,12 +257,14 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
         T s0 = T(0), s1 = T(0);
         unsigned flags = 0;
         if (xout) {
-            T *fout = (T *)L.f[(n + 1) & 1];
             const unsigned o = (unsigned)y * (unsigned)nx + (unsigned)x;
 #pragma unroll
             for (int k = 0; k < Q; ++k)
 #pragma unroll
-                for (int c = 0; c < M; ++c) sto(fout + (size_t)(k * M + c) * ps, o, Fk[k][c]);
+                for (int c = 0; c < M; ++c) {
+                    const T v[1] = {Fk[k][c]};
+                    io.st(k * M + c, o, v);
+                }
             Prim<T> qn;
             primitives<SYS, D, T>(Un, P, qn);
             const T v0 = max_speed<SYS, T>(0, qn, P), v1 = max_speed<SYS, T>(1, qn, P);
