@@ -111,10 +111,15 @@ std::string check_config(const arlbm_config *c)
 //   FP32 advection 0.0650 -> 0.0558, shallow water 0.520 -> 0.493,
 //        Euler 0.1758 -> 0.1777, reactive Euler 0.290 -> 0.298;
 //   FP64 shallow water 1.177 -> 1.140, Euler 0.388 -> 0.430.
-// The faster width is taken per system and precision.
+// The faster width is taken per system and precision.  FP64 advection takes
+// two columns where its two population buffers exceed the 256 MiB last-level
+// cache, and its rows come from HBM (us, one -> two: 2048^2 91.0 -> 78.3,
+// 4096^2 317 -> 290; inside the cache 1000^2 18.8 -> 20.1, 1700^2 39.6 -> 42.1).
 int columns_per_lane(const arlbm_config *c)
 {
     if (c->dim != 2 || c->nx % 2 != 0) return 1;
+    if (c->system == ARLBM_ADVECTION && c->precision == ARLBM_F64)
+        return 2 * 5 * (int64_t)sizeof(double) * c->nx * c->ny > ((int64_t)256 << 20) ? 2 : 1;
     static const int f32[4] = {2, 1, 2, 1}, f64[4] = {1, 1, 2, 1};  // advection, Euler, shallow water, reactive
     return (c->precision == ARLBM_F64 ? f64 : f32)[c->system];
 }

@@ -1173,16 +1173,16 @@ __device__ __forceinline__ void strip2d(const LatticeDesc &L, int64_t iter, int 
     };
 
     // Every population row is read from memory once and kept until the
-    // collision two rows later uses it.  FP32 keeps the rows in a register
-    // ring (4 Q m V registers).  FP64 would need twice the registers: with an
-    // LDS buffer (lds != nullptr) rows j-1 and j go to two LDS slots of the
-    // wave (the row in flight stays in registers); without one it reads the
-    // row again in the iteration that collides it, from L2 when it is still
-    // there (measured: mostly not, 2.2x the algorithmic reads at 2048^2).
-    // FP32 reactive Euler (25 values per row) also reads rows again: its
-    // step is bound by the kinetics' arithmetic, and the LDS slots measured
-    // 3.5% slower there (0.281 -> 0.291 ms at 2048^2).
-    constexpr bool kRing = sizeof(T) == 4 && Q * M <= 20;
+    // collision two rows later uses it.  Up to 100 bytes of populations per
+    // cell (FP32; FP64 advection) the rows are kept in a register ring (4 Q m V
+    // registers).  The other FP64 systems would need too many registers: with
+    // an LDS buffer (lds != nullptr) rows j-1 and j go to two LDS slots of the
+    // wave (the row in flight stays in registers); without one the row is read
+    // again in the iteration that collides it, from L2 when it is still there
+    // (measured: mostly not, 2.2x the algorithmic reads at 2048^2).  Rows read
+    // again against kept in the ring, 2048^2: FP32 reactive Euler (25 values
+    // per row) 254 -> 227 us per step, FP64 advection 103 -> 90.6.
+    constexpr bool kRing = Q * M * (int)sizeof(T) <= 100;
     const bool use_lds = sizeof(T) == 8 && lds != nullptr;
     // The ring's rotation copies a row still in flight, so the row loop waits
     // for its loads within the step.  Unrolling the loop by the ring's period
@@ -1566,9 +1566,9 @@ __device__ __forceinline__ int logical_wave()
 
 // FP64 2D steps keep two population rows per wave in LDS (measured per step
 // at 2048^2 and 4096^2: Euler 0.375 -> 0.318 ms, shallow water 1.086 ->
-// 0.909, reactive 0.517 -> 0.493, advection 0.117 -> 0.126, so advection,
-// whose rows are 5 values, reads them again; kernels whose slots would not
-// fit the CU's 160 KB of LDS do too).  Elements of one wave's two slots:
+// 0.909, reactive 0.517 -> 0.493; advection, whose rows are 5 values, keeps
+// them in registers; kernels whose slots would not fit the CU's 160 KB of LDS
+// read rows again).  Elements of one wave's two slots:
 template <int SYS, typename T, int V>
 __host__ __device__ constexpr int lds_ring_elems()
 {
@@ -1613,7 +1613,7 @@ __device__ __forceinline__ void seg2d_cpl(const LatticeDesc &L, int64_t iter, co
 {
     // the widths the single-lattice path takes per system and precision
     // (two columns per lane need an even nx)
-    constexpr bool kTwo = SYS == 2 || (SYS == 0 && sizeof(T) == 4);
+    constexpr bool kTwo = SYS == 2 || SYS == 0;
     if (kTwo && L.cpl == 2) seg2d<SYS, BED, T, kTwo ? 2 : 1>(L, iter, g, lds);
     else seg2d<SYS, BED, T, 1>(L, iter, g, lds);
 }

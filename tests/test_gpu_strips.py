@@ -238,3 +238,28 @@ def test_steps_write_only_lattice_cells(name, prec):
         f"flags {st['flags']}")
     assert ok
     assert np.array_equal(U, Uref)
+
+
+@pytest.mark.parametrize("nx,ny", [(2048, 1638), (2048, 1640), (2047, 1640)])
+def test_fp64_advection_strip_width_by_size(nx, ny):
+    """FP64 advection of even nx runs two columns per lane where its two
+    population buffers exceed 256 MiB (2048 x 1640 cells; 2048 x 1638 stay
+    below): alone and served, bit for bit the oracle."""
+    require_gpu()
+    p = crop(W.advection_sine_2d(n=2048, ax=0.8, ay=-0.5), nx, ny, bc=(T, T, T, T), steps=3)
+    say(f"[strips FP64 advection {nx}x{ny}]")
+    Lo = ora_from(p, parallel=True)
+    Lo.run(p.steps)
+    Uo = Lo.moments()
+    G = gpu_lattice(p, A.F64)
+    G.step(p.steps)
+    assert np.array_equal(G.moments(), Uo)
+    G.close()
+    srv = A.Server(1 << 30, A.F64)
+    rid = srv.submit(A.config_from(p, precision=A.F64), p.U0, None, p.steps)
+    done = []
+    while not done:
+        srv.iterate(8)
+        done = srv.poll(4)
+    srv.close()
+    assert done[0]["id"] == rid and np.array_equal(done[0]["U"].reshape(Uo.shape), Uo)
