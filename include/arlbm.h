@@ -331,7 +331,9 @@ int arlbm_server_destroy(arlbm_server *s);
 
 /* The batched launch's work list for lattices of configurations cfgs[0..n-1]
  * served together (3D lattices, which run launches of their own, take no
- * part), for a launch of at most `waves` waves, computed on the host as the
+ * part; neither do 2D lattices while they are so few and small that the
+ * server steps each in a launch of tiles, which this list does not show), for
+ * a launch of at most `waves` waves, computed on the host as the
  * server computes it (no GPU needed).  On return the list has *nsegs items
  * and the launch *nwaves waves; item k is segs[4k .. 4k+3] = (lattice index,
  * strip, first row, end row) for a 2D lattice, (lattice index, first strip,

@@ -202,14 +202,18 @@ int num_cus()
 // 12.0, 31 against 24, 63 against 41, 87 against 71), but for shallow water,
 // whose march of two columns per lane is the slower (23.8 against 29.1, FP64
 // 50.3 against 54.7).
+constexpr int64_t kTileWaves = 40, kTileWavesSwe = 64;
+int64_t tile_waves(int64_t nx, int64_t ny, int32_t rows, int64_t cus)
+{
+    const int64_t out = rows - 2 * kHalo, tiles = (nx + kOutW - 1) / kOutW * ((ny + out - 1) / out);
+    return rows * ((tiles + cus - 1) / cus);
+}
 int32_t choose_tile_rows(const arlbm_config *c, int64_t cus)
 {
-    const int64_t ncols = (c->nx + kOutW - 1) / kOutW;
     int32_t best = 0;
-    int64_t best_waves = c->system == ARLBM_SWE ? 64 : 40;
+    int64_t best_waves = c->system == ARLBM_SWE ? kTileWavesSwe : kTileWaves;
     for (int32_t rows = kMaxTileRows; rows >= 8; --rows) {
-        const int64_t out = rows - 2 * kHalo, tiles = ncols * ((c->ny + out - 1) / out);
-        const int64_t waves = rows * ((tiles + cus - 1) / cus);
+        const int64_t waves = tile_waves(c->nx, c->ny, rows, cus);
         if (waves <= best_waves) {
             best = rows;
             best_waves = waves;
@@ -1111,6 +1115,7 @@ struct Resident {
     void *dev;       // the lattice's device block (pool)
     size_t dev_cls;  // its size class
     double *dst;     // caller memory for the result, or nullptr
+    bool own = false;  // stepped by a launch of its own (rebuild_table)
 };
 struct Done {
     arlbm_completion c;
@@ -1612,15 +1617,46 @@ SchedLattice sched_lattice(int32_t i, const LatticeDesc &d)
     return {i, true, d.ncols, 1, (int64_t)kWave * 3 * m + kStrip1dLatency};
 }
 
+// Whether the resident 2D lattices are few and small enough that a tiled
+// launch for each (tile2d.hpp) beats the batched launch, whose waves march
+// bands of at least 8 rows however little there is to do.  A tiled step costs
+// its waves per CU and about 8 more for its launch, and the batched launch
+// that 1D lattices then still need about 12; the line is the one of a lattice
+// alone (choose_tile_rows).  Served, us per step, batched -> tiles: one 256^2
+// Euler lattice FP32 21.1 -> 9.2, FP64 34.9 -> 12.2, two of them 21.6 -> 17.8
+// and 35.8 -> 25.0 (three are past the line: batched 22.6 and 36.3), one beside
+// a 20000-cell 1D lattice 21.3 -> 14.9; 600^2 shallow water FP32 30.8 -> 19.2.
+bool step_in_tiles(const std::vector<LatticeDesc> &descs)
+{
+    int64_t cost = 0, line = kTileWavesSwe;
+    bool any = false, one_d = false;
+    for (const LatticeDesc &d : descs) {
+        if (own_launch(d)) continue;
+        if (d.variant < V_ADV2) {
+            one_d = true;
+            continue;
+        }
+        if (d.tile_rows == 0) return false;
+        any = true;
+        if (d.variant != V_SWE2) line = kTileWaves;
+        cost += tile_waves(d.nx, d.ny, d.tile_rows, num_cus()) + 8;
+    }
+    return any && cost + (one_d ? 12 : 0) <= line + 8;
+}
+
 int rebuild_table(arlbm_server *s)
 {
     std::vector<LatticeDesc> descs;
     std::vector<SchedLattice> lats;
-    for (size_t i = 0; i < s->resident.size(); ++i) {
-        LatticeDesc d = s->resident[i].lat->desc;
-        d.iter0 = s->resident[i].iter0;
+    for (Resident &r : s->resident) {
+        LatticeDesc d = r.lat->desc;
+        d.iter0 = r.iter0;
         descs.push_back(d);
-        if (!own_launch(d)) lats.push_back(sched_lattice((int32_t)i, d));
+    }
+    const bool tiles = step_in_tiles(descs);
+    for (size_t i = 0; i < descs.size(); ++i) {
+        s->resident[i].own = own_launch(descs[i]) || (tiles && descs[i].variant >= V_ADV2);
+        if (!s->resident[i].own) lats.push_back(sched_lattice((int32_t)i, descs[i]));
     }
     // one schedule per launch group, laid out after the descriptors
     int64_t ng = 0;
@@ -2175,9 +2211,10 @@ extern "C" int arlbm_server_iterate_n(arlbm_server *s, int32_t max_launches, int
         }
         if (e != hipSuccess) return sfail(s, ARLBM_EDEVICE, std::string("batched launch: ") + hipGetErrorString(e));
         // lattices outside the batched kernel (3D; 2D beyond 4 GiB of
-        // populations) run their own step after it, on the same stream
+        // populations; few and small 2D ones, in tiles) run their own step
+        // after it, on the same stream
         for (const Resident &r : s->resident) {
-            if (!own_launch(r.lat->desc)) continue;
+            if (!r.own) continue;
             LatticeDesc d = r.lat->desc;
             d.iter0 = r.iter0;
             e = s->precision == ARLBM_F64 ? f64::step_single(d, s->iter, s->stream)
