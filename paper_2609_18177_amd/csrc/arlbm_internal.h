@@ -17,20 +17,34 @@ constexpr int kOutW = kWave - 2 * kHalo;  // 58
 __host__ __device__ constexpr int strip_halo(int v) { return (kHalo + v - 1) / v * v; }
 __host__ __device__ constexpr int strip_out_w(int v) { return kWave * v - 2 * strip_halo(v); }
 static_assert(strip_out_w(1) == kOutW && strip_out_w(2) == 120, "strip geometry");
-// The one-workgroup march of a small 1D lattice: at most kMarchWaves waves, of
-// one cell per lane where 58 cells a wave hold the lattice, else of two (one
-// cell per lane is the faster wherever both hold it: Euler FP32 400 cells 1.67
-// against 1.70 us per step, 100 cells 1.08 against 1.51).  Two cells per lane
-// beat one launch per step (4.1-4.7 us) for advection and for FP32 Euler and
-// shallow water (at 1920 cells 1.13-1.73, 3.95 and 3.14 us); FP64 Euler and
-// shallow water (6.2 and 5.7 against 5.3 us) and the reactive system (7.3
-// against 5.8, 17.5 against 7.3) lose, so they march up to 928 cells.
+// The march of 1D lattices in registers (k_march1d).  One workgroup of at most
+// kMarchWaves waves, of one cell per lane where 58 cells a wave hold the
+// lattice (Euler FP32 400 cells 1.67 against 1.70 us per step of two, 100 cells
+// 1.08 against 1.51), else, for advection, of two (1920 cells FP32 1.13 us,
+// FP64 1.73, against 1.94 and 2.55 over several workgroups).  Larger lattices
+// march over several workgroups: for Euler and shallow water beyond 928 cells
+// (FP32 2.66 against 2.77 us there, FP64 3.86 against 3.75; two cells per lane
+// at 1500 cells 3.89 against 2.69), for the reactive system, bound by one CU's
+// kinetics, earlier (FP64 400 cells 5.6 against 5.5, 928 9.2 against 6.1; FP32
+// 600 3.8 against 3.9, 928 4.5 against 4.0).
 constexpr int kMarchWaves = 16;
 __host__ __device__ constexpr int march_width(int64_t nx) { return nx <= kMarchWaves * strip_out_w(1) ? 1 : 2; }
 constexpr int march_cells(int system, bool f64)
 {
-    return kMarchWaves * strip_out_w(system == 0 || (!f64 && system != 3) ? 2 : 1);
+    return system == 0 ? kMarchWaves * strip_out_w(2) : (system == 3 ? (f64 ? 7 : 12) : kMarchWaves) * kOutW;
 }
+// Several workgroups: four waves each (one per SIMD), more waves only past
+// kGridBlocks workgroups, which are all resident at once.  The exchange grows
+// with their number (us per step, one launch per step against the march: Euler
+// FP32 14800 cells 4.54 / 3.11, 40000 4.72 / 4.18, 100000 5.53 / 5.23, 118000
+// 5.61 / 5.58; FP64 14800 5.30 / 4.10, 29000 5.41 / 4.84, 40000 5.59 / 5.42,
+// 50000 5.62 / 5.89), which sets the largest lattices.
+constexpr int kGridWaves = 7, kGridBlocks = 256;
+constexpr int64_t grid_march_cells(bool f64) { return (int64_t)(f64 ? 160 * 4 : kGridBlocks * kGridWaves) * kOutW; }
+// Steps from which the several workgroups pay for their launch (us for 16 / 32
+// steps of 4096 Euler cells, one launch per step against one: FP32 82 / 149
+// against 79 / 123, FP64 90 / 172 against 96 / 158).
+constexpr int kGridMinSteps = 32;
 constexpr int kMaxTileRows = 16;          // rows (waves) of a tile of the tiled 2D step
 constexpr int kBlock = 256;               // 4 independent waves per block
 constexpr int kWavesPerBlock = kBlock / kWave;
@@ -131,6 +145,7 @@ constexpr int kQueueStride = 32;
                     hipStream_t s);                                                                    \
     hipError_t step_single(const LatticeDesc &h, int64_t iter, hipStream_t s);                        \
     hipError_t steps1d(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s);           \
+    hipError_t steps1d_grid(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s);      \
     hipError_t step_batched(const LatticeDesc *d_descs, const Segment *d_segs, const int32_t *d_qstart, \
                             unsigned *d_counters, int32_t parity, int32_t nwaves, int64_t iter,        \
                             hipStream_t s);                                                            \

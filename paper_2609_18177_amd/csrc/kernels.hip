@@ -185,22 +185,53 @@ static hipError_t march_impl(const LatticeDesc &h, int64_t iter0, int32_t nsteps
     const int v = march_width(h.nx), ow = strip_out_w(v), nw = (h.nx + ow - 1) / ow;
     constexpr int kTwo = march_cells(SYS, sizeof(real) == 8) > kMarchWaves * strip_out_w(1) ? 2 : 1;
     if (v == 2)
-        hipLaunchKernelGGL((k_march1d<SYS, real, kTwo>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
+        hipLaunchKernelGGL((k_march1d<SYS, real, kTwo, false>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
     else
-        hipLaunchKernelGGL((k_march1d<SYS, real, 1>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
+        hipLaunchKernelGGL((k_march1d<SYS, real, 1, false>), dim3(1), dim3(kWave * nw), 0, s, h, iter0, nsteps);
     return hipGetLastError();
 }
 
+// The march over several workgroups; an error leaves nothing launched that
+// changes the state, and the caller takes one launch per step.
+template <int SYS>
+static hipError_t grid_march_impl(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
+{
+    const int waves = (h.nx + kOutW - 1) / kOutW;
+    const int bw = waves <= 4 * kGridBlocks ? 4 : (waves + kGridBlocks - 1) / kGridBlocks;
+    const int nb = (waves + bw - 1) / bw;
+    const int64_t n = grid_march_words<SYS, real>(nb);
+    if (h.nx > grid_march_cells(sizeof(real) == 8) || nb < 2 || bw > kGridWaves ||
+        n * 8 > (int64_t)SysInfo<SYS, 1>::M * h.pstride * (int64_t)sizeof(real))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_clear_words<real>), dim3(cell_grid(n)), dim3(kBlock), 0, s, (unsigned long long *)h.u[0],
+                       (unsigned long long *)h.u[1], n);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    LatticeDesc d = h;
+    void *args[] = {&d, &iter0, &nsteps};
+    return hipLaunchCooperativeKernel((const void *)&k_march1d<SYS, real, 1, true>, dim3(nb), dim3(kWave * bw), args, 0,
+                                      s);
+}
+
+#define ARLBM_DISPATCH1(v, CALL)                 \
+    switch (v) {                                 \
+    case V_ADV1: return CALL<0>(h, iter0, nsteps, s); \
+    case V_EUL1: return CALL<1>(h, iter0, nsteps, s); \
+    case V_SWE1: return CALL<2>(h, iter0, nsteps, s); \
+    case V_REU1: return CALL<3>(h, iter0, nsteps, s); \
+    default: return hipErrorInvalidValue;        \
+    }
+
 hipError_t steps1d(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
 {
-    switch (h.variant) {
-    case V_ADV1: return march_impl<0>(h, iter0, nsteps, s);
-    case V_EUL1: return march_impl<1>(h, iter0, nsteps, s);
-    case V_SWE1: return march_impl<2>(h, iter0, nsteps, s);
-    case V_REU1: return march_impl<3>(h, iter0, nsteps, s);
-    default: return hipErrorInvalidValue;
-    }
+    ARLBM_DISPATCH1(h.variant, march_impl)
 }
+
+hipError_t steps1d_grid(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
+{
+    ARLBM_DISPATCH1(h.variant, grid_march_impl)
+}
+#undef ARLBM_DISPATCH1
 
 hipError_t step_batched(const LatticeDesc *d_descs, const Segment *d_segs, const int32_t *d_qstart,
                         unsigned *d_counters, int32_t parity, int32_t nwaves, int64_t iter, hipStream_t s)

@@ -731,18 +731,38 @@ extern "C" int arlbm_set_state_device(arlbm_lattice *h, const double *U0, const 
     return set_state_impl(h, U0, bed, true, t0);
 }
 
-// Enqueue n steps.  A small 1D lattice takes them in launches of up to
-// kMarchRun steps of one workgroup (k_march1d), the same bits as one launch
-// per step.
+// Enqueue n steps.  A 1D lattice takes them in launches of up to kMarchRun
+// steps (k_march1d; the same bits as one launch per step): of one workgroup, or,
+// for kGridMinSteps steps and more of a larger lattice, cooperative ones of
+// several.  A cooperative launch is not made while the stream is captured, and
+// where it is refused the steps are launched one by one.
 constexpr int32_t kMarchRun = 1024;
 static hipError_t enqueue_steps(arlbm_lattice *h, int64_t n)
 {
-    const bool march = h->cfg.dim == 1 && n >= 2 && h->cfg.nx <= march_cells(h->cfg.system, is_f64(h));
+    const bool one = h->cfg.dim == 1 && n >= 2 && h->cfg.nx <= march_cells(h->cfg.system, is_f64(h));
+    bool grid = h->cfg.dim == 1 && !one && n >= kGridMinSteps && h->cfg.nx <= grid_march_cells(is_f64(h));
+    if (grid) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        grid = hipStreamIsCapturing(h->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!grid) (void)hipGetLastError();
+    }
     while (n > 0) {
-        const int32_t k = march ? (int32_t)std::min<int64_t>(n, kMarchRun) : 1;
-        hipError_t e = !march ? L_step(h, h->step)
-                              : (is_f64(h) ? f64::steps1d(h->desc, h->step, k, h->stream)
-                                           : f32::steps1d(h->desc, h->step, k, h->stream));
+        int32_t k = one || grid ? (int32_t)std::min<int64_t>(n, kMarchRun) : 1;
+        hipError_t e;
+        if (grid) {
+            e = is_f64(h) ? f64::steps1d_grid(h->desc, h->step, k, h->stream)
+                          : f32::steps1d_grid(h->desc, h->step, k, h->stream);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                grid = false;
+                continue;
+            }
+        } else if (one) {
+            e = is_f64(h) ? f64::steps1d(h->desc, h->step, k, h->stream)
+                          : f32::steps1d(h->desc, h->step, k, h->stream);
+        } else {
+            e = L_step(h, h->step);
+        }
         if (e != hipSuccess) return e;
         h->step += k;
         n -= k;

@@ -543,6 +543,13 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // go to memory once, after the last step, as one launch per step leaves them.
 // Lanes outside the lattice's halo hold the nearest halo cell, so that no
 // lane ever computes on an undefined state.
+// GRID: the same march over the workgroups of a cooperative launch, for
+// lattices one CU is too small for.  A workgroup's outer cells and its bound
+// go to the others through memory, in the two moment buffers in turn (in 1D
+// they serve the read-back only), each word carrying its step's number, so
+// that no fence and no grid barrier is needed.  A set is rewritten two steps
+// later, by a workgroup that has heard every bound of the step between, which
+// is told only after its teller has read all it needs of the set.
 // What bounds a step: the dependent chain of one wave (LDS read, bound
 // reduction, FP64 time step, indicator, collision, LDS write, barrier) while
 // every SIMD has one wave (up to 232 cells), one CU's instruction issue above.
@@ -550,22 +557,89 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // steps, and (above 928 cells) one launch per step: advection FP64 256 cells
 // 2.38 -> 0.78, Euler FP32 928 4.45 -> 2.66, FP64 6.61 -> 3.86, shallow water
 // FP64 600 4.81 -> 2.82, reactive FP64 256 7.84 -> 5.36; two cells per lane at
-// 1920 cells: advection FP32 4.06 -> 1.13, Euler FP32 4.41 -> 3.95.
+// 1920 cells: advection FP32 4.06 -> 1.13.  GRID against one launch per step
+// (about 1.2 us of a step are the exchange): 4096 cells Euler FP32 4.33 ->
+// 2.88, FP64 4.91 -> 3.92, shallow water FP32 4.43 -> 2.61, reactive FP64 7.14
+// -> 6.23, advection FP32 3.94 -> 1.90; 14800 cells Euler FP32 4.33 -> 3.13.
 template <int SYS>
 __host__ __device__ constexpr int march_values()
 {
     return 3 * SysInfo<SYS, 1>::M + (SYS == 0 ? 0 : (SYS == 3 ? 4 : 3));
 }
-template <int SYS, typename T, int V>
-__global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, int64_t iter0, int32_t nsteps)
+// A value and the step it belongs to in one 8-byte word (FP64: its halves in
+// two), stored and loaded whole: a reader that finds its step's number has the
+// value, with no fence and no flag beside it.
+template <typename T>
+constexpr int kTellWords = sizeof(T) / 4;
+template <typename T>
+__device__ __forceinline__ void tell(unsigned long long *o, T v, unsigned tag)
+{
+    const unsigned long long t = (unsigned long long)tag << 32;
+    if constexpr (sizeof(T) == 4) {
+        __hip_atomic_store(o, t | __builtin_bit_cast(unsigned, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+        __hip_atomic_store(o, t | (unsigned)b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(o + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+// N values of the step `tag`; false when they have not come after some ten
+// seconds (the launch is cooperative, so the writers run, and a step takes
+// microseconds; the bound only makes the end certain).
+template <int N, typename T>
+__device__ __forceinline__ bool hear(unsigned long long *o, T *v, unsigned tag)
+{
+    constexpr int W = kTellWords<T>;
+    for (int tries = 0; tries < (1 << 24); ++tries) {
+        unsigned long long w[N * W];
+        bool all = true;
+#pragma unroll
+        for (int i = 0; i < N * W; ++i) w[i] = __hip_atomic_load(o + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < N * W; ++i) all = all && (unsigned)(w[i] >> 32) == tag;
+        if (all) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (W == 1) v[i] = __builtin_bit_cast(T, (unsigned)w[i]);
+                else v[i] = __builtin_bit_cast(T, (w[2 * i + 1] << 32) | (unsigned)w[2 * i]);
+            }
+            return true;
+        }
+    }
+    return false;
+}
+// 8-byte words of one of the two sets the workgroups exchange: the three outer
+// cells on each side of each, and its bound on a 128-byte line of its own
+// (packed to 8 bytes the bounds of 63 workgroups took 3600 cells of Euler FP32
+// from 2.93 to 3.97 us per step).
+constexpr int kBoundWords = 16;
+template <int SYS, typename T>
+__host__ __device__ constexpr int64_t grid_march_words(int blocks)
+{
+    return (int64_t)blocks * (2 * kHalo * march_values<SYS>() * kTellWords<T> + kBoundWords);
+}
+// Clears the words before a launch (step numbers start at 1).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_clear_words(unsigned long long *a, unsigned long long *b, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        a[i] = b[i] = 0ull;
+}
+
+template <int SYS, typename T, int V, bool GRID>
+__global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_march1d(LatticeDesc L, int64_t iter0,
+                                                                                      int32_t nsteps)
 {
     constexpr int D = 1, M = SysInfo<SYS, 1>::M, Q = 3, NV = march_values<SYS>(), HC = strip_halo(V);
+    constexpr int kWords = kTellWords<T>;
     __shared__ T edge[2][kMarchWaves][2 * kHalo][NV];
     __shared__ T bound[2][kMarchWaves];
+    const int blk = GRID ? (int)blockIdx.x : 0, nblk = GRID ? (int)gridDim.x : 1;
     const int lane = (int)(threadIdx.x & (kWave - 1)), wave = (int)(threadIdx.x >> 6);
-    const int nw = (int)(blockDim.x >> 6), nx = L.nx;
+    const int bw = (int)(blockDim.x >> 6), nw = GRID ? bw * nblk : bw, nx = L.nx;
+    const int gwave = GRID ? blk * bw + wave : wave;  // the wave's place in the lattice
     auto first_cell = [&](int w) { return (int)((int64_t)w * nx / nw); };
-    const int c0 = first_cell(wave), c1 = first_cell(wave + 1);
+    const int c0 = first_cell(gwave), c1 = first_cell(gwave + 1);
     const int64_t n0 = iter0 - L.iter0;
     const DevScalars *sc = L.sc;
     const Phys<T> P = make_phys<T>(L);
@@ -578,6 +652,7 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
     int to[V];          // the LDS slot an own cell is published in, or -1
     unsigned xo[V];
     bool own[V], rx[V];
+    int far[V], give[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         x[v] = c0 - HC + lane * V + v;
@@ -589,8 +664,15 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
         while (first_cell(ow + 1) <= xm) ++ow;
         const int rel = xm - first_cell(ow), right = first_cell(ow + 1) - kHalo - first_cell(ow);
         const int k = rel < kHalo ? rel : kHalo + (rel > right ? rel - right : 0);
-        from[v] = own[v] ? -1 : ow * (2 * kHalo) + k;
+        from[v] = own[v] ? -1 : (GRID ? ow % bw : ow) * (2 * kHalo) + k;
         to[v] = own[v] && (rel < kHalo || rel >= right) ? wave * (2 * kHalo) + k : -1;
+        if constexpr (GRID) {
+            // cells of another workgroup, and cells another one reads, through memory
+            far[v] = !own[v] && ow / bw != blk ? ow / bw * (2 * kHalo) + k : -1;
+            give[v] = to[v] >= 0 && ((wave == 0 && rel < kHalo) || (wave == bw - 1 && rel >= right))
+                          ? blk * (2 * kHalo) + k
+                          : -1;
+        }
     }
 
     T f[V][Q][M], U[V][M], db[V];
@@ -610,6 +692,30 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
         o[V - 1] = from_right(a[0]);
 #pragma unroll
         for (int v = 0; v < V - 1; ++v) o[v] = a[v + 1];
+    };
+    // a halo cell's populations and primitives as its owner published them
+    auto take = [&](int v, const T (&e)[NV]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k)
+#pragma unroll
+            for (int c = 0; c < M; ++c) f[v][k][c] = e[k * M + c];
+        moments(v);
+        if constexpr (SYS != 0) {
+            q[v].rho = U[v][0];
+            q[v].vel[0] = rx[v] ? -e[Q * M] : e[Q * M];
+            q[v].c = q[v].cL = e[Q * M + 2];
+            if constexpr (SYS == 2) {
+                q[v].mom[0] = rx[v] ? -e[Q * M + 1] : e[Q * M + 1];
+            } else {
+                q[v].mom[0] = U[v][1];
+                q[v].E = U[v][2];
+                q[v].p = e[Q * M + 1];
+            }
+            if constexpr (SYS == 3) {
+                q[v].Z = U[v][M - 1];
+                q[v].Y = e[Q * M + 3];
+            }
+        }
     };
     {
         const T *fin = (const T *)L.f[n0 & 1];
@@ -797,6 +903,24 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
                     if constexpr (SYS == 3) e[Q * M + 3] = q[v].Y;
                 }
             }
+            if constexpr (GRID) {
+                if (give[v] >= 0) {
+                    T e[NV];
+#pragma unroll
+                    for (int k = 0; k < Q; ++k)
+#pragma unroll
+                        for (int c = 0; c < M; ++c) e[k * M + c] = f[v][k][c];
+                    if constexpr (SYS != 0) {
+                        e[Q * M] = q[v].vel[0];
+                        e[Q * M + 1] = SYS == 2 ? q[v].mom[0] : q[v].p;
+                        e[Q * M + 2] = q[v].cL;
+                        if constexpr (SYS == 3) e[Q * M + 3] = q[v].Y;
+                    }
+                    unsigned long long *o = (unsigned long long *)L.u[set] + (size_t)give[v] * NV * kWords;
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) tell(o + i * kWords, e[i], (unsigned)(s + 1));
+                }
+            }
         }
         __syncthreads();
         T m = bound[set][lane & (kMarchWaves - 1)];
@@ -804,32 +928,43 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
         m = max_step<0x112, 0xf>(m);
         m = max_step<0x114, 0xf>(m);
         m = max_step<0x118, 0xf>(m);
-        ab = (double)read_lane(m, kMarchWaves - 1);
+        if constexpr (GRID) {
+            // every workgroup's bound: lane i hears workgroups i, i + 64, ..
+            unsigned long long *o = (unsigned long long *)L.u[set] + (size_t)nblk * 2 * kHalo * NV * kWords;
+            const T mine = read_lane(m, kMarchWaves - 1);
+            if (wave == 0 && lane == 0) tell(o + (size_t)blk * kBoundWords, mine, (unsigned)(s + 1));
+            T got = mine;
+            bool ok = true;
+            for (int j = lane; j < nblk; j += kWave) {
+                T other;
+                ok = hear<1>(o + (size_t)j * kBoundWords, &other, (unsigned)(s + 1)) && ok;
+                got = other > got ? other : got;
+            }
+            T e[V][NV];
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (far[v] >= 0)
+                    ok = hear<NV>((unsigned long long *)L.u[set] + (size_t)far[v] * NV * kWords, e[v], (unsigned)(s + 1)) && ok;
+            if (__ballot(!ok)) {  // a workgroup has not answered: give the run up
+                flags |= 1u;
+                if (bad == ~0ull) bad = (unsigned long long)n - null0;
+                break;
+            }
+            ab = (double)wave_max<T>(got);
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (far[v] >= 0) take(v, e[v]);
+        } else {
+            ab = (double)read_lane(m, kMarchWaves - 1);
+        }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            if (from[v] >= 0) {
-                const T *e = &edge[set][0][0][0] + from[v] * NV;
+            if (from[v] >= 0 && !(GRID && far[v] >= 0)) {
+                const T *l = &edge[set][0][0][0] + from[v] * NV;
+                T e[NV];
 #pragma unroll
-                for (int k = 0; k < Q; ++k)
-#pragma unroll
-                    for (int c = 0; c < M; ++c) f[v][k][c] = e[k * M + c];
-                moments(v);
-                if constexpr (SYS != 0) {
-                    q[v].rho = U[v][0];
-                    q[v].vel[0] = rx[v] ? -e[Q * M] : e[Q * M];
-                    q[v].c = q[v].cL = e[Q * M + 2];
-                    if constexpr (SYS == 2) {
-                        q[v].mom[0] = rx[v] ? -e[Q * M + 1] : e[Q * M + 1];
-                    } else {
-                        q[v].mom[0] = U[v][1];
-                        q[v].E = U[v][2];
-                        q[v].p = e[Q * M + 1];
-                    }
-                    if constexpr (SYS == 3) {
-                        q[v].Z = U[v][M - 1];
-                        q[v].Y = e[Q * M + 3];
-                    }
-                }
+                for (int i = 0; i < NV; ++i) e[i] = l[i];
+                take(v, e);
             }
         }
     }
@@ -852,7 +987,7 @@ __global__ __launch_bounds__(kMarchWaves * kWave) void k_march1d(LatticeDesc L, 
         atomicOr(&so->flags, any);
         atomicMin(&so->first_bad_step, bad);
     }
-    if (wave == 0) {
+    if (gwave == 0) {
         if (lane == 0) {
             so->t[(ne + 2) % 3] = s == nsteps ? t_before : t;
             so->t[ne % 3] = t;

@@ -1,8 +1,11 @@
-"""The one-workgroup march of small 1D lattices (state in registers, halos and
-bounds through LDS) against one launch per step, bit for bit: sizes where the
-deal of cells to waves and lanes can go wrong (one wave, the first cell of a
-second wave, the last size of one and of two cells per lane, too large for the
-march), every face, and time-targeted runs that stop inside a launch."""
+"""The march of 1D lattices in registers (halos and bounds through LDS in one
+workgroup, through memory between several) against one launch per step, bit for
+bit: sizes where the deal of cells to waves, lanes and workgroups can go wrong
+(one wave, the first cell of a second wave, the last size of one and of two
+cells per lane, two workgroups, one more than a workgroup's waves, more bounds
+than lanes, five waves a workgroup), every face, time-targeted runs that stop
+inside a launch, several lattices on streams of their own, and a captured
+stream, where the steps are launched one by one."""
 import numpy as np
 import pytest
 
@@ -56,3 +59,77 @@ def test_march_equals_single_steps(kind, face, prec):
         assert np.array_equal(a.moments(), b.moments()), n
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("kind,face", [("advection", A.PERIODIC), ("euler", A.REFLECTIVE), ("euler", A.PERIODIC),
+                                       ("swe", A.REFLECTIVE), ("reactive", A.TRANSMISSIVE)])
+def test_march_over_several_workgroups(kind, face, prec):
+    require_gpu()
+    # 15000 cells: 65 workgroups, more than lanes; 60000 in FP32: 1035 waves, five a workgroup
+    for n in (407, 697, 929, 1921, 4096, 15000, 60000):
+        p = _problem(kind, n, face)
+        say(f"[grid march {kind} face={face} prec={prec}] {n} cells")
+        a, b = (gpu_lattice(p, prec) for _ in range(2))
+        a.step(35)
+        for _ in range(35):
+            b.step(1)
+        sa, sb = a.sync(check=False), b.sync(check=False)
+        assert sa == sb and np.array_equal(a.moments(), b.moments()), n
+        goal = sa["t"] + 40.5 * sa["last_dt"]
+        k = a.step_until(goal)
+        a.step(33)
+        for _ in range(k + 33):
+            b.step(1)
+        sa, sb = a.sync(check=False), b.sync(check=False)
+        assert sa == sb and np.array_equal(a.moments(), b.moments()), n
+        a.close()
+        b.close()
+
+
+def test_march_on_several_streams():
+    """Lattices stepped at the same time on streams of their own."""
+    import torch
+
+    require_gpu()
+    ps = [_problem("euler", n, A.TRANSMISSIVE) for n in (4096, 9000, 30000, 2000, 14000, 50000)]
+    want, got, lats = [], [], []
+    for p in ps:
+        L = gpu_lattice(p, A.F32)
+        for _ in range(200):
+            L.step(1)
+        want.append(L.moments())
+        L.close()
+    for p in ps:
+        L = A.Lattice(A.config_from(p, precision=A.F32), stream=torch.cuda.Stream())
+        L.set_state(p.U0)
+        lats.append(L)
+    for _ in range(4):
+        for L in lats:
+            L.step(50)
+    got = [L.moments() for L in lats]
+    say("[grid march] six streams", [bool(np.array_equal(a, b)) for a, b in zip(got, want)])
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))
+
+
+def test_march_in_a_captured_stream():
+    """Steps recorded into a graph run when it is launched, as one launch per step."""
+    import torch
+
+    require_gpu()
+    p = _problem("euler", 4096, A.TRANSMISSIVE)
+    ref = gpu_lattice(p, A.F32)
+    ref.step(40)
+    want = ref.moments()
+    ref.close()
+    s = torch.cuda.Stream()
+    L = A.Lattice(A.config_from(p, precision=A.F32), stream=s)
+    L.set_state(p.U0)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        L.step(40)
+    g.replay()
+    torch.cuda.synchronize()
+    assert np.array_equal(L.moments(), want)
+    L.close()
