@@ -1354,7 +1354,7 @@ bool own_launch(const LatticeDesc &d) { return d.variant >= V_ADV3 || (d.variant
 // small as keeps bands of at most 256 rows, and every 2D lattice is cut into
 // bands of equal height, about h = (strip rows) / (r waves) rows (at least
 // 8); in a single round h is the lowest height whose items all fit the
-// waves.  A lattice alone thus gets the single-lattice kernel's bands, one
+// waves, and lattices of slower rows take fewer of them (lattice_band).  A lattice alone thus gets the single-lattice kernel's bands, one
 // per wave (2048^2 Euler: 28 bands of 74 rows of its 36 strips); a large mix
 // gets about r items per wave, which the queues balance.  Lattices with the
 // tallest bands come first.  Each part holds a contiguous range of the bands
@@ -1388,6 +1388,7 @@ bool own_launch(const LatticeDesc &d) { return d.variant >= V_ADV3 || (d.variant
 // down each strip put the waves of one XCD at scattered rows (2048^2 Euler
 // 51% slower than the single-lattice kernel).
 constexpr int kWarmRows2d = 6, kWarmStrips1d = 2, kMinRows2d = 8, kMaxRows2d = 256;
+constexpr double kStrip1dRows = 1.2;
 constexpr int64_t kStrip1dLatency = 1280, kRowValues = 1280, kRun1dMix = 8;
 
 int64_t batched_waves() { return 4 * (int64_t)num_cus(); }  // one wave per SIMD
@@ -1398,11 +1399,31 @@ struct SchedLattice {
     int32_t ncols;  // strips
     int64_t ny;     // 2D rows
     int64_t unit;   // cost per row (2D) or per strip (1D)
+    double weight;  // 2D: time of a marched row beside one of Euler's
 };
+
+// Band height of lattice l in a one-launch schedule.  Over several rounds
+// every band is h rows.  In one round the launch lasts as long as its slowest
+// wave, and a row's time differs from system to system: the lattice whose rows
+// are the lightest (weight wmin) takes h rows, the others as many as take that
+// long, warm-up rows included.
+int64_t lattice_band(const SchedLattice &l, int64_t h, int64_t r, double wmin)
+{
+    if (r == 1 && l.weight > wmin)
+        h = std::max<int64_t>(kMinRows2d, (int64_t)((double)(h + kWarmRows2d) * wmin / l.weight) - kWarmRows2d);
+    return std::min(h, l.ny);
+}
 
 // The band height h of a one-launch schedule for these lattices and its
 // rounds r (items per wave): the lowest height at most kMaxRows2d that puts
 // at most one item on every wave, else two or more rounds.
+double lightest_row(const std::vector<SchedLattice> &lats)
+{
+    double w = HUGE_VAL;
+    for (const SchedLattice &l : lats)
+        if (!l.one_d) w = std::min(w, l.weight);
+    return w;
+}
 void band_height(const std::vector<SchedLattice> &lats, int64_t W, int64_t &h, int64_t &r)
 {
     int64_t S = 0;  // 2D strip rows
@@ -1411,19 +1432,32 @@ void band_height(const std::vector<SchedLattice> &lats, int64_t W, int64_t &h, i
     h = kMaxRows2d;
     r = 1;
     if (S > 0) {
+        const double wmin = lightest_row(lats);
         r = std::max<int64_t>(1, (S + W * kMaxRows2d - 1) / (W * kMaxRows2d));
         h = std::max<int64_t>(kMinRows2d, (S + W * r - 1) / (W * r));
         auto items_at = [&](int64_t hh) {
             int64_t n = 0;
-            for (const SchedLattice &l : lats)
-                if (!l.one_d) n += (int64_t)l.ncols * ((l.ny + std::min(hh, l.ny) - 1) / std::min(hh, l.ny));
+            for (const SchedLattice &l : lats) {
+                if (l.one_d) continue;
+                const int64_t hl = lattice_band(l, hh, 1, wmin);
+                n += (int64_t)l.ncols * ((l.ny + hl - 1) / hl);
+            }
             return n;
+        };
+        // waves left for the 1D strips, a strip about 1.2 rows: dealt to the
+        // ends of bands that all end together they ended the launch late (three
+        // shallow-water, two Euler and one 1D lattice 52.4 us; so 43.5)
+        int64_t strips1d = 0;
+        for (const SchedLattice &l : lats)
+            if (l.one_d) strips1d += l.ncols;
+        auto room = [&](int64_t hh) {
+            return W - std::min<int64_t>(W / 2, (int64_t)(kStrip1dRows * (double)strips1d / (double)(hh + kWarmRows2d)));
         };
         if (r == 1) {
             // one round: the lowest height whose items all fit the waves (a
             // second round for a few items would double the step time)
-            while (items_at(h) > W && h < kMaxRows2d) ++h;
-            if (items_at(h) > W) {
+            while (items_at(h) > room(h) && h < kMaxRows2d) ++h;
+            if (items_at(h) > room(h)) {
                 r = 2;
                 h = std::max<int64_t>(kMinRows2d, (S + W * r - 1) / (W * r));
             }
@@ -1440,6 +1474,7 @@ int64_t build_schedule(const std::vector<SchedLattice> &lats, int64_t W, std::ve
     qstart.assign(kQueues + 1, 0);
     int64_t h, r;
     band_height(lats, W, h, r);
+    const double wmin = lightest_row(lats);
     // each lattice in bands of equal height, at most h; lattices with the
     // tallest bands first
     struct Item {
@@ -1450,7 +1485,7 @@ int64_t build_schedule(const std::vector<SchedLattice> &lats, int64_t W, std::ve
     std::vector<std::pair<int64_t, const SchedLattice *>> order;  // (band height, lattice)
     for (const SchedLattice &l : lats) {
         if (l.one_d) continue;
-        const int64_t hl = std::min(h, l.ny);
+        const int64_t hl = lattice_band(l, h, r, wmin);
         const int64_t nb = (l.ny + hl - 1) / hl;
         order.push_back({(l.ny + nb - 1) / nb, &l});
     }
@@ -1628,13 +1663,31 @@ std::vector<int32_t> launch_groups(const std::vector<SchedLattice> &lats, int64_
     return grp;
 }
 
+// Time of a marched row of a strip beside one of Euler's in the same
+// precision, between what bands of 8 rows (latency) and large lattices
+// (bandwidth) show: shallow water of two columns per lane 1.39-1.57 FP32,
+// 1.58 FP64, of one 0.95; reactive 1.5-1.7; advection 0.4-0.6.  Mixes of
+// Euler, shallow-water and 1D lattices in bands of one height took, us per
+// step, and with these weights take: 16 lattices FP32 156 -> 124, FP64 315 ->
+// 240; 10 lattices 230 -> 175, 463 -> 344; 24 lattices 231 -> 188, 465 -> 373
+// (0.85-1.05 and 1.35-1.9 for the two widths: within 5% of these).
+double row_weight(const LatticeDesc &d, bool f64)
+{
+    switch (d.variant) {
+    case V_ADV2: return f64 ? 0.4 : 0.55;
+    case V_SWE2: return d.cpl == 2 ? 1.6 : 0.95;
+    case V_REU2: return 1.6;
+    default: return 1.0;
+    }
+}
+
 // A schedule item of lattice i from its descriptor (1D and 2D lattices the
 // batched kernel steps).
-SchedLattice sched_lattice(int32_t i, const LatticeDesc &d)
+SchedLattice sched_lattice(int32_t i, const LatticeDesc &d, bool f64)
 {
     const int m = num_fields(d.variant % 4, d.variant / 4 + 1);
-    if (d.variant >= V_ADV2) return {i, false, d.ncols, d.ny, (int64_t)kWave * d.cpl * 5 * m};
-    return {i, true, d.ncols, 1, (int64_t)kWave * 3 * m + kStrip1dLatency};
+    if (d.variant >= V_ADV2) return {i, false, d.ncols, d.ny, (int64_t)kWave * d.cpl * 5 * m, row_weight(d, f64)};
+    return {i, true, d.ncols, 1, (int64_t)kWave * 3 * m + kStrip1dLatency, 1.0};
 }
 
 // Whether the resident 2D lattices are few and small enough that a tiled
@@ -1676,7 +1729,7 @@ int rebuild_table(arlbm_server *s)
     const bool tiles = step_in_tiles(descs);
     for (size_t i = 0; i < descs.size(); ++i) {
         s->resident[i].own = own_launch(descs[i]) || (tiles && descs[i].variant >= V_ADV2);
-        if (!s->resident[i].own) lats.push_back(sched_lattice((int32_t)i, descs[i]));
+        if (!s->resident[i].own) lats.push_back(sched_lattice((int32_t)i, descs[i], s->precision == ARLBM_F64));
     }
     // one schedule per launch group, laid out after the descriptors
     int64_t ng = 0;
@@ -2333,7 +2386,7 @@ std::string plan_lattices(const arlbm_config *cfgs, int32_t n, std::vector<Sched
         d.cpl = columns_per_lane(&cfgs[i]);
         d.ncols = (int32_t)((cfgs[i].nx + strip_out_w(d.cpl) - 1) / strip_out_w(d.cpl));
         d.ny = (int32_t)cfgs[i].ny;
-        lats.push_back(sched_lattice(i, d));
+        lats.push_back(sched_lattice(i, d, cfgs[i].precision == ARLBM_F64));
     }
     return "";
 }

@@ -265,3 +265,37 @@ def test_launch_groups_few_waves(waves):
         sub = [c for c, k in zip(cfgs, grp) if k == g]
         qs, segs, nw = A.plan_schedule(sub, waves)
         _check_cover(sub, qs, segs)
+
+
+@pytest.mark.parametrize("precision", [A.F32, A.F64])
+@pytest.mark.parametrize("sides,n1d", [((700, 300), 0), ((700, 301, 300), 0), ((1000, 600, 300, 501), 30000), ((130, 80), 60000)])
+def test_one_round_of_mixed_systems_ends_together(sides, n1d, precision):
+    """Euler and shallow-water lattices in one round: every cell once, every
+    band a wave's first item, and the lattices whose rows take longer (shallow
+    water of two columns per lane, 1.6 times an Euler row; of one 0.95) in
+    bands that take about as long as Euler's, 6 warm-up rows included, unless
+    they are at the 8-row minimum; beside 1D lattices some waves stay free of
+    bands."""
+    cfgs = [A.config_from((W.euler_seeded_2d if i % 2 == 0 else W.swe_bed_2d)(i, n=n), precision=precision)
+            for i, n in enumerate(sides)]
+    if n1d:
+        cfgs.append(A.config_from(W.euler_seeded_1d(0, n=n1d), precision=precision))
+    qs, segs, nw = A.plan_schedule(cfgs, WAVES)
+    _check_cover(cfgs, qs, segs)
+    bands = _two_d_items(cfgs, segs)
+    assert bands <= WAVES and (not n1d or bands < WAVES)
+    assert max(len(p) for p in _queue_parts(cfgs, qs, segs)) <= WAVES // 8
+    weight = [1.0 if c.system == A.EULER else (1.6 if _strips(c)[1] == 2 else 0.95) for c in cfgs]
+    time, height = {}, {}
+    for i, c in enumerate(cfgs):
+        if c.dim == 2:
+            mine = segs[segs[:, 0] == i]
+            height[i] = int((mine[:, 3] - mine[:, 2]).max())
+            time[i] = (height[i] + 6) * weight[i]
+    longest = max([t for i, t in time.items() if height[i] > 8], default=0.0)
+    for i in time:
+        # the rows are dealt evenly to the fewest bands of at most the share's
+        # height, so one band fewer would exceed the share
+        nb = -(-cfgs[i].ny // height[i])
+        fewer = cfgs[i].ny if nb == 1 else -(-cfgs[i].ny // (nb - 1))
+        assert height[i] == 8 or nb == 1 or longest <= (fewer + 6) * weight[i], (i, time, height)
