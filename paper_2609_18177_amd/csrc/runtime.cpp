@@ -11,6 +11,7 @@
 #include <sys/mman.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <climits>
@@ -329,9 +330,9 @@ void par_copy(void *dst, const void *src, size_t bytes)
 }
 
 // Host <-> device copies of large pageable arrays (the plain path's state
-// upload and read-back): the data moves through two pinned chunks used in
-// turn, the host copy of one chunk (several threads) overlapping the DMA of
-// the other.  The chunk pairs are kept for the process in a free list, one
+// upload and read-back): the data moves through pinned chunks used in turn,
+// the host copy of one chunk (several threads) overlapping the DMA of
+// another.  The chunk pairs are kept for the process in a free list, one
 // pair per transfer in progress.  Arrays below kBounceMin go directly.
 constexpr size_t kBounceChunk = (size_t)16 << 20, kBounceMin = (size_t)8 << 20;
 std::mutex g_bounce_mu;
@@ -389,8 +390,71 @@ hipError_t copy_h2d(void *dst, const void *src, size_t bytes, hipStream_t st)
     return e;
 }
 
+// Host copies of a transfer's chunks by a team of threads that lives as long
+// as the transfer: the chunks are cut into slices, taken in order; a slice
+// waits until its chunk is open (its DMA has landed) and counts itself done.
+struct CopyTeam {
+    static constexpr size_t kChunks = 4, kChunk = 2 * kBounceChunk / kChunks, kSlice = (size_t)1 << 20;
+    static_assert(kChunk % kSlice == 0, "a slice lies in one chunk");
+    char *dst;
+    const char *buf;
+    size_t bytes;
+    std::atomic<size_t> next{0}, open{0};
+    std::atomic<bool> stop{false};
+    std::atomic<size_t> done[kChunks] = {};  // bytes copied out of each part of the pinned pair, from the start on
+    std::vector<std::thread> th;
+
+    CopyTeam(void *dst_, const char *buf_, size_t bytes_) : dst((char *)dst_), buf(buf_), bytes(bytes_) {}
+    void work()
+    {
+        for (;;) {
+            const size_t off = next.fetch_add(1) * kSlice;
+            if (off >= bytes) return;
+            const size_t c = off / kChunk, len = std::min(kSlice, bytes - off);
+            while (open.load(std::memory_order_acquire) <= c) {
+                if (stop.load(std::memory_order_relaxed)) return;
+                std::this_thread::yield();
+            }
+            std::memcpy(dst + off, buf + (c % kChunks) * kChunk + (off - c * kChunk), len);
+            done[c % kChunks].fetch_add(len, std::memory_order_release);
+        }
+    }
+    void start(size_t n)  // without a thread, wait() copies
+    {
+        try {
+            th.reserve(n);
+            for (size_t t = 0; t < n; ++t) th.emplace_back([this] { work(); });
+        } catch (...) {
+            // fewer threads than asked for
+        }
+    }
+    void land(size_t c) { open.store(c + 1, std::memory_order_release); }  // chunk c is in its buffer
+    void wait(size_t c)  // until chunk c is copied
+    {
+        const size_t b = c % kChunks, len = std::min(kChunk, bytes - c * kChunk);
+        if (th.empty()) {
+            std::memcpy(dst + c * kChunk, buf + b * kChunk, len);
+            return;
+        }
+        const size_t all = c / kChunks * kChunk + len;  // this chunk and those before it in its part
+        while (done[b].load(std::memory_order_acquire) < all) std::this_thread::yield();
+    }
+    void join()
+    {
+        stop.store(true);
+        for (auto &x : th) x.join();
+        th.clear();
+    }
+    ~CopyTeam() { join(); }
+};
+
 // dst (host) <- src (device) after the work ordered before it on the stream;
-// returns with dst written.
+// returns with dst written.  The pinned pair is used as four chunks in turn:
+// while the team copies one out, the next are in the DMA's queue.  The team
+// starts when the first chunk has landed, so it never waits for the work
+// before the transfer.  (Two chunks of twice the size, each copied by threads
+// started for it, read 134 MB in 4.5 ms, 403 in 13.0 and 671 in 21.1; so they
+// take 3.6, 10.5 and 15.5, the DMA alone 2.4, 7.1 and 11.8.)
 hipError_t copy_d2h(void *dst, const void *src, size_t bytes, hipStream_t st)
 {
     char *buf = bytes >= kBounceMin ? bounce_take() : nullptr;
@@ -398,25 +462,31 @@ hipError_t copy_d2h(void *dst, const void *src, size_t bytes, hipStream_t st)
         hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
         return e == hipSuccess ? hipStreamSynchronize(st) : e;
     }
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    hipError_t e = hipEventCreateWithFlags(&ev[0], hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[1], hipEventDisableTiming);
-    const size_t nchunks = (bytes + kBounceChunk - 1) / kBounceChunk;
-    auto enqueue = [&](size_t k) {
-        const int b = (int)(k & 1);
-        const size_t off = k * kBounceChunk, len = std::min(kBounceChunk, bytes - off);
-        hipError_t r = hipMemcpyAsync(buf + b * kBounceChunk, (const char *)src + off, len, hipMemcpyDeviceToHost, st);
+    constexpr size_t kChunks = CopyTeam::kChunks, kChunk = CopyTeam::kChunk;
+    const size_t nchunks = (bytes + kChunk - 1) / kChunk;
+    CopyTeam team(dst, buf, bytes);
+    hipEvent_t ev[kChunks] = {};
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < kChunks && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+    auto enqueue = [&](size_t c) {
+        const size_t b = c % kChunks, off = c * kChunk, len = std::min(kChunk, bytes - off);
+        hipError_t r = hipMemcpyAsync(buf + b * kChunk, (const char *)src + off, len, hipMemcpyDeviceToHost, st);
         return r == hipSuccess ? hipEventRecord(ev[b], st) : r;
     };
-    for (size_t k = 0; k < 2 && k < nchunks && e == hipSuccess; ++k) e = enqueue(k);
-    for (size_t k = 0; k < nchunks && e == hipSuccess; ++k) {
-        const int b = (int)(k & 1);
-        const size_t off = k * kBounceChunk, len = std::min(kBounceChunk, bytes - off);
-        e = hipEventSynchronize(ev[b]);
+    for (size_t c = 0; c < kChunks && c < nchunks && e == hipSuccess; ++c) e = enqueue(c);
+    for (size_t c = 0; c < nchunks && e == hipSuccess; ++c) {
+        e = hipEventSynchronize(ev[c % kChunks]);
         if (e != hipSuccess) break;
-        par_copy((char *)dst + off, buf + b * kBounceChunk, len);
-        if (k + 2 < nchunks) e = enqueue(k + 2);  // into the chunk just emptied
+        if (c == 0) team.start(std::min<size_t>(8, std::max(1u, std::thread::hardware_concurrency())));
+        team.land(c);
+        if (c > 0) {
+            team.wait(c - 1);
+            if (c - 1 + kChunks < nchunks) e = enqueue(c - 1 + kChunks);  // into the chunk just emptied
+        }
     }
+    if (e == hipSuccess) team.wait(nchunks - 1);
+    team.join();
+    // the chunks idle before the pair goes back to the free list
     const hipError_t es = hipStreamSynchronize(st);
     if (e == hipSuccess) e = es;
     for (hipEvent_t x : ev)
