@@ -46,7 +46,8 @@ METRIC = "GLUPS + HBM GB/s, FP32 batched vs FP64 plain; p50/p99 solve latency"
 # the kernels, their build, and the runtime that deals the batched kernel's
 # work (its schedule decides the batched launch's traffic)
 KERNEL_SOURCES = ["paper_2609_18177_amd/csrc/step.hpp", "paper_2609_18177_amd/csrc/physics.hpp",
-                  "paper_2609_18177_amd/csrc/step3d.hpp", "paper_2609_18177_amd/csrc/kernels.hip",
+                  "paper_2609_18177_amd/csrc/step3d.hpp", "paper_2609_18177_amd/csrc/tile2d.hpp",
+                  "paper_2609_18177_amd/csrc/tile3d.hpp", "paper_2609_18177_amd/csrc/kernels.hip",
                   "paper_2609_18177_amd/csrc/runtime.cpp", "paper_2609_18177_amd/build.py"]
 ONLY = ["euler2d_batched_f32", "euler2d_f32", "euler2d_f64", "swe2d_batched_f32", "swe2d_f32", "euler3d_f32",
         "serving", "serving_fixed_f32"]

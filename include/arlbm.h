@@ -158,16 +158,19 @@ int arlbm_create(const arlbm_config *cfg, const arlbm_buffers *bufs, void *strea
  * meet; the checks of large states run on several host threads).
  * Initialises f = f^eq(U0) with the step-0 coefficients and synchronises the
  * stream.  Arrays of 8 MB and more move through two pinned 16 MB chunks of
- * the library's, used in turn. */
+ * the library's, used in turn (read-back: four of 8 MB). */
 int arlbm_set_state(arlbm_lattice *h, const double *U0, const double *bed, double t0);
 
 /* Same, with U0 (and bed) already on the device as FP64 planes. */
 int arlbm_set_state_device(arlbm_lattice *h, const double *U0_dev, const double *bed_dev,
                            double t0);
 
-/* Enqueue n time steps (asynchronous: one kernel launch per step on the
- * handle's stream, no host round trip).  Device-side problems are latched in
- * the status flags and reported by arlbm_sync. */
+/* Enqueue n time steps on the handle's stream (asynchronous, no host round
+ * trip): one kernel launch per step in 2D and 3D; in 1D one launch takes up to
+ * 1024 steps where the lattice fits the device's registers (above 928 cells
+ * or so by a cooperative launch, which exchanges words through the two moment
+ * buffers, so not on a stream under capture).  Device-side problems are latched
+ * in the status flags and reported by arlbm_sync. */
 int arlbm_step(arlbm_lattice *h, int64_t n);
 
 /* Whole steps until the simulated time reaches t_final (t >= t_final; the

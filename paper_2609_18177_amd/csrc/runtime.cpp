@@ -1424,9 +1424,10 @@ bool own_launch(const LatticeDesc &d) { return d.variant >= V_ADV3 || (d.variant
 // small as keeps bands of at most 256 rows, and every 2D lattice is cut into
 // bands of equal height, about h = (strip rows) / (r waves) rows (at least
 // 8); in a single round h is the lowest height whose items all fit the
-// waves, and lattices of slower rows take fewer of them (lattice_band).  A lattice alone thus gets the single-lattice kernel's bands, one
-// per wave (2048^2 Euler: 28 bands of 74 rows of its 36 strips); a large mix
-// gets about r items per wave, which the queues balance.  Lattices with the
+// waves, and lattices of slower rows take fewer of them (lattice_band).  A
+// lattice alone thus gets the single-lattice kernel's bands, one per wave
+// (2048^2 Euler: 28 bands of 74 rows of its 36 strips); a large mix gets
+// about r items per wave, which the queues balance.  Lattices with the
 // tallest bands come first.  Each part holds a contiguous range of the bands
 // (equal counts in one round, so that every band is a wave's first item;
 // about equal work over several rounds), then every kQueues-th 1D run, the
