@@ -133,3 +133,31 @@ def test_march_in_a_captured_stream():
     torch.cuda.synchronize()
     assert np.array_equal(L.moments(), want)
     L.close()
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("kind", ["euler", "swe", "reactive"])
+def test_time_target_from_the_initial_state(kind, prec):
+    """From a state no step was taken from, the length of the first launch
+    comes from the initial wave speeds, with half as many steps in reserve:
+    the last launch ends at the target, inside it, and a cap on the steps
+    falls before or inside the reserve.  928 cells: the march's last size."""
+    require_gpu()
+    for n in (4, 59, 928):
+        p = _problem(kind, n, A.REFLECTIVE)
+        say(f"[march to a time {kind} prec={prec}] {n} cells")
+        a, b, c = (gpu_lattice(p, prec) for _ in range(3))
+        b.step(1)
+        goal = 60.5 * b.sync(check=False)["last_dt"]
+        k = 1
+        while k < 500 and b.sync(check=False)["t"] < goal:
+            b.step(1)
+            k += 1
+        assert a.step_until(goal) == k, n
+        sa, sb = a.sync(check=False), b.sync(check=False)
+        assert sa == sb and np.array_equal(a.moments(), b.moments()), n
+        assert c.step_until(goal, max_steps=k - 1) == k - 1, n
+        assert c.step_until(goal, max_steps=k + 9) == 1, n
+        assert c.sync(check=False) == sb and np.array_equal(c.moments(), b.moments()), n
+        for x in (a, b, c):
+            x.close()
