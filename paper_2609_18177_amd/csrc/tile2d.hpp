@@ -90,8 +90,23 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
         }
     T b = T(0);
     if constexpr (BED) b = ((const T *)L.bed)[off];
-    // the coefficients, once per tile, by a wave that has no more to do than its moments
-    if (w == rows - 1) {
+    // The coefficients, once per tile, by the last wave, which has no indicator
+    // to form: beside the others' (kBeside) or, before the first barrier, while
+    // they wait for their rows.  There everybody waits for its chain of
+    // quotients too (us per step, before -> beside: 64^2 Euler FP32 6.4 -> 5.9,
+    // FP64 8.3 -> 7.7; 256^2 9.2 -> 8.7, 12.2 -> 11.6; 512^2 shallow water FP64
+    // 27.6 -> 26.3); but advection's indicator is too short to cover it, and the
+    // reactive kernels lack the registers (FP32 80 -> 83, one tile per CU: 400^2
+    // 15.3 -> 16.8; FP64 spills: 256^2 18.2 -> 18.6).
+    constexpr bool kBeside = SYS == 1 || SYS == 2;
+    if constexpr (kBeside) {
+        if (stopped(L, n)) {  // the state carries over (a step that is not defined is flagged here too)
+            Coefs<T> cf;
+            if (step_coefs<D, T>(L, n, cf)) null_copy<T>(L, n, Q * M, x, xout && yout, y, y + 1, item == 0 && w == 0);
+            else if (item == 0 && w == 0 && lane == 0) flag_degenerate(L, n);
+            return;
+        }
+    } else if (w == rows - 1) {
         Coefs<T> cf;
         const bool ok = step_coefs<D, T>(L, n, cf);
         if (lane == 0) {
@@ -121,14 +136,25 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
     Prim<T> q;
     primitives<SYS, D, T>(U, P, q);
     __syncthreads();
-    const int state = __builtin_amdgcn_readfirstlane(sh.state);
-    if (state != 0) {
-        if (state == 1) {
-            if (item == 0 && w == 0 && lane == 0) flag_degenerate(L, n);
-        } else {
-            null_copy<T>(L, n, Q * M, x, xout && yout, y, y + 1, item == 0 && w == 0);
+    if constexpr (kBeside) {
+        if (w == rows - 1) {
+            Coefs<T> cf;
+            const bool ok = step_coefs<D, T>(L, n, cf);
+            if (lane == 0) {
+                if (ok) sh.cf = cf;
+                sh.state = !ok;
+            }
         }
-        return;
+    } else {
+        const int state = __builtin_amdgcn_readfirstlane(sh.state);
+        if (state != 0) {
+            if (state == 1) {
+                if (item == 0 && w == 0 && lane == 0) flag_degenerate(L, n);
+            } else {
+                null_copy<T>(L, n, Q * M, x, xout && yout, y, y + 1, item == 0 && w == 0);
+            }
+            return;
+        }
     }
     if (w >= 1 && w < rows - 1) {
         T nu = T(0);
@@ -154,6 +180,12 @@ __global__ __launch_bounds__(kMaxTileRows * kWave) void k_tile2d(LatticeDesc L, 
         lnu[w * kWave + lane] = nu;
     }
     __syncthreads();
+    if constexpr (kBeside) {
+        if (__builtin_amdgcn_readfirstlane(sh.state)) {
+            if (item == 0 && w == 0 && lane == 0) flag_degenerate(L, n);
+            return;
+        }
+    }
     const Coefs<T> cf = sh.cf;
     T fs[Q][M], dbx = T(0), dby = T(0);
     if (w >= 2 && w < rows - 2) {
