@@ -58,3 +58,34 @@ def test_tiles_against_oracle_and_served(system, bc, nx, ny):
     U = G.moments()
     assert np.array_equal(U, _served_beside(p, LARGE)) and np.array_equal(U, _served(p, p.steps))
     G.close()
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("system", ["euler", "swe", "reactive"])
+def test_tiles_without_a_step(system, prec):
+    """Launches that take no step: at the stop time the state carries over;
+    with wave-speed bounds of zero (every density NaN) the degenerate flag is
+    raised, at the stop time too."""
+    require_gpu()
+    p = crop(MAKE[system](), 70, 41, bc=(T,) * 4, ox=93, oy=107, steps=1)
+    G = gpu_lattice(p, prec)
+    G.step(3)
+    st = G.sync(check=False)
+    assert G.step_until(st["t"] + 0.5 * st["last_dt"]) == 1  # and one launch at the stop time
+    H = gpu_lattice(p, prec)
+    H.step(4)
+    assert G.sync(check=False) == H.sync(check=False) and np.array_equal(G.moments(), H.moments())
+    H.close()
+    st = G.sync(check=False)
+    blob = bytearray(G.save_state())
+    real = np.float32 if prec == A.F32 else np.float64
+    cells = np.full(p.nx * p.ny, np.nan, dtype=real).tobytes()
+    blob[56:56 + len(cells)] = cells  # f_0 of the first field, after the header
+    G.load_state(bytes(blob))
+    say(f"[no step {system} prec={prec}]")
+    # a step to NaN, and a launch that is flagged, so not counted as at the stop time
+    assert G.step_until(st["t"] + 0.5 * st["last_dt"], max_steps=2) == 2
+    bad = G.sync(check=False)
+    assert bad["flags"] & A.FLAG_NONFINITE and bad["flags"] & A.FLAG_DEGENERATE
+    assert bad["first_bad_step"] == 4 and bad["step"] == 6
+    G.close()
