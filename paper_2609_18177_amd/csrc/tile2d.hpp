@@ -6,9 +6,9 @@
 // but below it every lattice takes the same 11-60 us.  What bounds this one:
 // the launch and one memory latency (about 5 us) up to 128^2, then the
 // instruction issue of the tiles' rows, halo rows included.  us per step, march
-// -> tiles: 64^2 Euler FP32 19.4 -> 6.4, FP64 32.1 -> 8.4, shallow water FP64
-// 52.8 -> 8.2; 256^2 Euler FP32 20.1 -> 9.1, FP64 34.4 -> 12.1; 400^2 reactive
-// FP32 34.1 -> 15.5.
+// -> tiles: 64^2 Euler FP32 19.4 -> 5.8, FP64 32.1 -> 7.7, shallow water FP64
+// 52.8 -> 7.2; 256^2 Euler FP32 20.1 -> 8.6, FP64 34.4 -> 11.6; 400^2 reactive
+// FP32 34.1 -> 15.3.
 //
 // A tile of `rows` waves writes rows - 6 rows of 58 columns; the outer three
 // rows and lanes on each side are its halo.  Row w of the tile:

@@ -14,8 +14,8 @@
 // What bounds it: the indicator over the halo (3.4 evaluations per cell; FP64
 // divisions) and, for a lattice of one round of tiles, the chain of its
 // stages.  us per step, march -> tiles: 24^3 Euler FP32 77 -> 13, FP64 143 ->
-// 18, 48^3 FP64 174 -> 29, 64^3 FP32 81 -> 32, FP64 179 -> 61, reactive FP64
-// 161 -> 95, advection FP32 28 -> 12.
+// 18, 48^3 FP64 174 -> 28, 64^3 FP32 81 -> 31, FP64 179 -> 59, reactive FP64
+// 161 -> 94, advection FP32 28 -> 12.
 #pragma once
 
 #include "step3d.hpp"
