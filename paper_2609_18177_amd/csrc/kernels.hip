@@ -201,10 +201,9 @@ static hipError_t grid_march_impl(const LatticeDesc &h, int64_t iter0, int32_t n
     const int nb = (waves + bw - 1) / bw;
     const int64_t n = grid_march_words<SYS, real>(nb);
     if (h.nx > grid_march_cells(sizeof(real) == 8) || nb < 2 || bw > kGridWaves ||
-        n * 8 > (int64_t)SysInfo<SYS, 1>::M * h.pstride * (int64_t)sizeof(real))
+        (n + kEntryWords) * 8 > (int64_t)SysInfo<SYS, 1>::M * h.pstride * (int64_t)sizeof(real))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_clear_words<real>), dim3(cell_grid(n)), dim3(kBlock), 0, s, (unsigned long long *)h.u[0],
-                       (unsigned long long *)h.u[1], n);
+    hipLaunchKernelGGL((k_open_march<real>), dim3(cell_grid(n)), dim3(kBlock), 0, s, h, iter0, n);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     LatticeDesc d = h;

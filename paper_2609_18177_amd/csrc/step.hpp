@@ -623,12 +623,31 @@ __host__ __device__ constexpr int64_t grid_march_words(int blocks)
 {
     return (int64_t)blocks * (2 * kHalo * march_values<SYS>() * kTellWords<T> + kBoundWords);
 }
-// Clears the words before a launch (step numbers start at 1).
+// What every wave of a launch starts from, behind the words of the first set.
+// No wave of the march may read it from the lattice's scalars: the first
+// workgroup rewrites those when it has done its last step, and a launch that
+// takes none (it starts at the stop time, or its bound is not defined) gives a
+// workgroup nothing to hear from the others, so one that starts late could find
+// its slot of bounds cleared or half rewritten.  The launch before forms the
+// copy, nobody writes it during the march, and what the march writes nobody
+// reads before the launch after it.
+struct MarchEntry {
+    double t, bound, last_dt;
+    unsigned long long null_launches;
+};
+constexpr int kEntryWords = sizeof(MarchEntry) / 8;
+// Clears the words before a march (step numbers start at 1) and forms its entry.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_clear_words(unsigned long long *a, unsigned long long *b, int64_t n)
+__global__ __launch_bounds__(kBlock) void k_open_march(LatticeDesc L, int64_t iter0, int64_t n)
 {
+    unsigned long long *a = (unsigned long long *)L.u[0], *b = (unsigned long long *)L.u[1];
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         a[i] = b[i] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+        const int slot = (int)((iter0 - L.iter0) % 3);
+        const double bound = abar_of(L, slot, 0);
+        if (threadIdx.x == 0) *(MarchEntry *)(a + n) = {L.sc->t[slot], bound, L.sc->last_dt, L.sc->null_launches};
+    }
 }
 
 template <int SYS, typename T, int V, bool GRID>
@@ -646,7 +665,6 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     auto first_cell = [&](int w) { return (int)((int64_t)w * nx / nw); };
     const int c0 = first_cell(gwave), c1 = first_cell(gwave + 1);
     const int64_t n0 = iter0 - L.iter0;
-    const DevScalars *sc = L.sc;
     const Phys<T> P = make_phys<T>(L);
     constexpr bool src = SYS == 2;
     const bool has_bed = src && L.bed != nullptr;
@@ -741,9 +759,12 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
 #pragma unroll
         for (int v = 0; v < V; ++v) db[v] = has_bed ? ddiv<T>(br[v] - bl[v], T(2) * P.dx) : T(0);
     }
-    double t = sc->t[n0 % 3], t_before = t, last_dt = sc->last_dt;
-    double ab = abar_of(L, (int)(n0 % 3), 0);
-    const unsigned long long null0 = sc->null_launches;
+    MarchEntry at;
+    if constexpr (GRID) at = *(const MarchEntry *)((const unsigned long long *)L.u[0] + grid_march_words<SYS, T>(nblk));
+    else at = {L.sc->t[n0 % 3], abar_of(L, (int)(n0 % 3), 0), L.sc->last_dt, L.sc->null_launches};
+    double t = at.t, t_before = t, last_dt = at.last_dt;
+    double ab = at.bound;
+    const unsigned long long null0 = at.null_launches;
     unsigned flags = 0;
     unsigned long long bad = ~0ull;
     Coefs<T> cf0;
@@ -977,9 +998,10 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     __syncthreads();
     const int64_t ne = n0 + nsteps;
     T *fout = (T *)L.f[ne & 1];
+    const bool there = s == 0 && (nsteps & 1) == 0;  // in the buffer it was read from, and others may still read it
 #pragma unroll
     for (int v = 0; v < V; ++v)
-        if (own[v])
+        if (own[v] && !there)
 #pragma unroll
             for (int k = 0; k < Q; ++k)
 #pragma unroll
