@@ -168,10 +168,19 @@ int arlbm_set_state_device(arlbm_lattice *h, const double *U0_dev, const double 
 /* Enqueue n time steps on the handle's stream (asynchronous, no host round
  * trip): one kernel launch per step in 2D and 3D; in 1D one launch takes up to
  * 1024 steps where the lattice fits the device's registers (above 928 cells
- * or so by a cooperative launch, which exchanges words through the two moment
- * buffers, so not on a stream under capture).  Device-side problems are latched
- * in the status flags and reported by arlbm_sync. */
+ * or so by workgroups that exchange words through the two moment buffers, for
+ * 32 steps and more, and not on a stream under capture).  Device-side problems
+ * are latched in the status flags and reported by arlbm_sync. */
 int arlbm_step(arlbm_lattice *h, int64_t n);
+
+/* Limits of the waits of a 1D launch of several workgroups, in looks of about
+ * a microsecond at what the others wrote.  gather_looks (65536 in a new
+ * handle): how long its first workgroups wait for all of them to run at the
+ * same time before they call it off; one workgroup then takes the steps, with
+ * the same results but slower (0: always).  hear_looks (2^24): how long a
+ * workgroup waits for another's words of a step, once all run, before it
+ * gives up.  The calls that step h after this one use them. */
+int arlbm_set_march_limits(arlbm_lattice *h, int32_t gather_looks, int32_t hear_looks);
 
 /* Whole steps until the simulated time reaches t_final (t >= t_final; the
  * last step is not shortened, which keeps the scheme second order) or until

@@ -90,6 +90,7 @@ def lib():
             "arlbm_set_state": ([vp, dp, dp, C.c_double], C.c_int),
             "arlbm_set_state_device": ([vp, vp, vp, C.c_double], C.c_int),
             "arlbm_step": ([vp, C.c_int64], C.c_int),
+            "arlbm_set_march_limits": ([vp, C.c_int32, C.c_int32], C.c_int),
             "arlbm_sync": ([vp, C.POINTER(Status)], C.c_int),
             "arlbm_step_until": ([vp, C.c_double, C.c_int64, C.POINTER(C.c_int64)], C.c_int),
             "arlbm_read_moments": ([vp, dp], C.c_int),
@@ -243,6 +244,10 @@ class Lattice:
 
     def step(self, n: int = 1):
         _check(lib().arlbm_step(self._h, int(n)), self._h)
+
+    def set_march_limits(self, gather_looks: int = 1 << 16, hear_looks: int = 1 << 24):
+        """Limits of the waits of 1D launches of several workgroups."""
+        _check(lib().arlbm_set_march_limits(self._h, int(gather_looks), int(hear_looks)), self._h)
 
     def step_until(self, t_final: float, max_steps: int = 10 ** 9) -> int:
         """Whole steps until t >= t_final; returns the number of steps taken."""

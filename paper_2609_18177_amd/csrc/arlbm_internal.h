@@ -33,18 +33,26 @@ constexpr int march_cells(int system, bool f64)
 {
     return system == 0 ? kMarchWaves * strip_out_w(2) : (system == 3 ? (f64 ? 7 : 12) : kMarchWaves) * kOutW;
 }
-// Several workgroups: four waves each (one per SIMD), more waves only past
-// kGridBlocks workgroups, which are all resident at once.  The exchange grows
+// Several workgroups: four waves each (one per SIMD), and at most a quarter of
+// what the device holds at once (kGridShare), so that the lattices of several
+// streams, of which a process runs four at a time by default, find room beside
+// each other: FP32 74240 cells (reactive 59392), FP64 37120 (reactive 29696).
+// The exchange grows
 // with their number (us per step, one launch per step against the march: Euler
 // FP32 14800 cells 4.54 / 3.11, 40000 4.72 / 4.18, 100000 5.53 / 5.23, 118000
 // 5.61 / 5.58; FP64 14800 5.30 / 4.10, 29000 5.41 / 4.84, 40000 5.59 / 5.42,
 // 50000 5.62 / 5.89), which sets the largest lattices.
-constexpr int kGridWaves = 7, kGridBlocks = 256;
-constexpr int64_t grid_march_cells(bool f64) { return (int64_t)(f64 ? 160 * 4 : kGridBlocks * kGridWaves) * kOutW; }
+constexpr int kGridWaves = 4, kGridShare = 4;
+constexpr int64_t grid_march_cells(bool f64) { return (int64_t)(f64 ? 160 : 320) * kGridWaves * kOutW; }
 // Steps from which the several workgroups pay for their launch (us for 16 / 32
 // steps of 4096 Euler cells, one launch per step against one: FP32 82 / 149
 // against 79 / 123, FP64 90 / 172 against 96 / 158).
 constexpr int kGridMinSteps = 32;
+// Looks of about 1 us at the words of other workgroups before one calls a march
+// off (60 ms, in which other work on the device lets the rest come to run) or,
+// in the march, gives it up.
+constexpr int kGatherLooks = 1 << 16, kHearLooks = 1 << 24;
+constexpr int kStripWaves = 16;           // waves of k_strips1d
 constexpr int kMaxTileRows = 16;          // rows (waves) of a tile of the tiled 2D step
 constexpr int kBlock = 256;               // 4 independent waves per block
 constexpr int kWavesPerBlock = kBlock / kWave;
@@ -109,6 +117,7 @@ struct LatticeDesc {
     int32_t omega_on;     // omega export plane present (else omega is null and never written)
     int32_t cpl;          // 2D: columns per lane of the step's strips (1, or 2 when nx is even)
     int32_t buf;          // 2D: population buffers below 4 GiB, addressed by buffer resources
+    int32_t gather_looks, hear_looks;  // 1D march over several workgroups: the limits of its waits
     int32_t abar_n;       // copies of each wave-speed slot in use: a power of two <= kAbarCopies, fixed per lattice
     double dx, cfl, eps, gamma, g, adv[3], h_dry, rho_floor, p_floor, omega_fixed;
     double q_heat, k_rate, t_act;  // reactive Euler: heat release, rate constant, activation temperature

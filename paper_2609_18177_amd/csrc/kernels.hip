@@ -191,25 +191,28 @@ static hipError_t march_impl(const LatticeDesc &h, int64_t iter0, int32_t nsteps
     return hipGetLastError();
 }
 
-// The march over several workgroups; an error leaves nothing launched that
-// changes the state, and the caller takes one launch per step.
+// The march over several workgroups: the launch that opens it, the march, and
+// the launch that takes the steps if it was called off.
+// hipErrorNotSupported: not for this lattice, and nothing was launched.
 template <int SYS>
 static hipError_t grid_march_impl(const LatticeDesc &h, int64_t iter0, int32_t nsteps, hipStream_t s)
 {
-    const int waves = (h.nx + kOutW - 1) / kOutW;
-    const int bw = waves <= 4 * kGridBlocks ? 4 : (waves + kGridBlocks - 1) / kGridBlocks;
-    const int nb = (waves + bw - 1) / bw;
+    static const int room = [] {
+        int per_cu = 0;
+        const auto fn = (const void *)&k_march1d<SYS, real, 1, true>;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kGridWaves * kWave, 0) != hipSuccess) return 0;
+        return per_cu * num_cus();
+    }();
+    const int waves = (h.nx + kOutW - 1) / kOutW, nb = (waves + kGridWaves - 1) / kGridWaves;
     const int64_t n = grid_march_words<SYS, real>(nb);
-    if (h.nx > grid_march_cells(sizeof(real) == 8) || nb < 2 || bw > kGridWaves ||
+    if (h.nx > grid_march_cells(sizeof(real) == 8) || nb < 2 || kGridShare * nb > room ||
         (n + kEntryWords) * 8 > (int64_t)SysInfo<SYS, 1>::M * h.pstride * (int64_t)sizeof(real))
-        return hipErrorInvalidValue;
+        return hipErrorNotSupported;
     hipLaunchKernelGGL((k_open_march<real>), dim3(cell_grid(n)), dim3(kBlock), 0, s, h, iter0, n);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    LatticeDesc d = h;
-    void *args[] = {&d, &iter0, &nsteps};
-    return hipLaunchCooperativeKernel((const void *)&k_march1d<SYS, real, 1, true>, dim3(nb), dim3(kWave * bw), args, 0,
-                                      s);
+    hipLaunchKernelGGL((k_march1d<SYS, real, 1, true>), dim3(nb), dim3(kWave * kGridWaves), 0, s, h, iter0, nsteps);
+    hipLaunchKernelGGL((k_strips1d<SYS, real>), dim3(1), dim3(kWave * kStripWaves), 0, s, h, iter0, nsteps,
+                       (const MarchGate *)((unsigned long long *)h.u[0] + n + kGateWord));
+    return hipGetLastError();
 }
 
 #define ARLBM_DISPATCH1(v, CALL)                 \

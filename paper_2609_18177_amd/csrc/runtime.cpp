@@ -729,6 +729,8 @@ extern "C" int arlbm_create(const arlbm_config *cfg, const arlbm_buffers *bufs, 
     d.band_h = cfg->dim == 2 ? choose_band(cfg->ny, d.ncols, resident_waves(cfg->precision, d.variant, d.cpl),
                                            4 * (int64_t)num_cus())
                              : 1;
+    d.gather_looks = kGatherLooks;
+    d.hear_looks = kHearLooks;
     d.tile_rows = cfg->dim == 2 ? choose_tile_rows(cfg, num_cus()) : 0;
     d.iter0 = 0;
     d.t_stop = HUGE_VAL;
@@ -803,9 +805,8 @@ extern "C" int arlbm_set_state_device(arlbm_lattice *h, const double *U0, const 
 
 // Enqueue n steps.  A 1D lattice takes them in launches of up to kMarchRun
 // steps (k_march1d; the same bits as one launch per step): of one workgroup, or,
-// for kGridMinSteps steps and more of a larger lattice, cooperative ones of
-// several.  A cooperative launch is not made while the stream is captured, and
-// where it is refused the steps are launched one by one.
+// for kGridMinSteps steps and more of a larger lattice, of several, and that not
+// while the stream is captured.
 constexpr int32_t kMarchRun = 1024;
 static hipError_t enqueue_steps(arlbm_lattice *h, int64_t n)
 {
@@ -822,8 +823,7 @@ static hipError_t enqueue_steps(arlbm_lattice *h, int64_t n)
         if (grid) {
             e = is_f64(h) ? f64::steps1d_grid(h->desc, h->step, k, h->stream)
                           : f32::steps1d_grid(h->desc, h->step, k, h->stream);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
+            if (e == hipErrorNotSupported) {
                 grid = false;
                 continue;
             }
@@ -847,6 +847,15 @@ extern "C" int arlbm_step(arlbm_lattice *h, int64_t n)
     if (n < 0) return fail(h, ARLBM_EINVAL, "n must be >= 0");
     const hipError_t e = enqueue_steps(h, n);
     if (e != hipSuccess) return hip_fail(h, e, "step launch");
+    return ARLBM_OK;
+}
+
+extern "C" int arlbm_set_march_limits(arlbm_lattice *h, int32_t gather_looks, int32_t hear_looks)
+{
+    if (!h) return fail(nullptr, ARLBM_EINVAL, "handle is NULL");
+    if (gather_looks < 0 || hear_looks < 0) return fail(h, ARLBM_EINVAL, "limits must be >= 0");
+    h->desc.gather_looks = gather_looks;
+    h->desc.hear_looks = hear_looks;
     return ARLBM_OK;
 }
 

@@ -548,8 +548,15 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // go to memory once, after the last step, as one launch per step leaves them.
 // Lanes outside the lattice's halo hold the nearest halo cell, so that no
 // lane ever computes on an undefined state.
-// GRID: the same march over the workgroups of a cooperative launch, for
-// lattices one CU is too small for.  A workgroup's outer cells and its bound
+// GRID: the same march over several workgroups, for lattices one CU is too
+// small for.  They wait for one another, so all must run at the same time:
+// gather() has shown that before any of them takes a step, and k_strips1d, the
+// launch after, takes the steps where it has not.  (A cooperative launch would
+// promise it, but those of a process run one after the other on one queue of
+// the device, which the caller's stream waits for and which waits for that:
+// four 4096-cell Euler lattices on streams of their own took 2.9 us per step
+// and lattice FP32, 4.1 FP64, and so take 0.8 and 1.2; one lattice 40 steps at a
+// time 3.5-6.5, so 3.2.)  A workgroup's outer cells and its bound
 // go to the others through memory, in the two moment buffers in turn (in 1D
 // they serve the read-back only), each word carrying its step's number, so
 // that no fence and no grid barrier is needed.  A set is rewritten two steps
@@ -588,14 +595,14 @@ __device__ __forceinline__ void tell(unsigned long long *o, T v, unsigned tag)
         __hip_atomic_store(o + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
-// N values of the step `tag`; false when they have not come after some ten
-// seconds (the launch is cooperative, so the writers run, and a step takes
-// microseconds; the bound only makes the end certain).
+// N values of the step `tag`; false when they have not come after `limit`
+// looks, some ten seconds (the writers run, and a step takes microseconds; the
+// limit only makes the end certain).
 template <int N, typename T>
-__device__ __forceinline__ bool hear(unsigned long long *o, T *v, unsigned tag)
+__device__ __forceinline__ bool hear(unsigned long long *o, T *v, unsigned tag, int limit)
 {
     constexpr int W = kTellWords<T>;
-    for (int tries = 0; tries < (1 << 24); ++tries) {
+    for (int tries = 0; tries < limit; ++tries) {
         unsigned long long w[N * W];
         bool all = true;
 #pragma unroll
@@ -635,7 +642,37 @@ struct MarchEntry {
     double t, bound, last_dt;
     unsigned long long null_launches;
 };
-constexpr int kEntryWords = sizeof(MarchEntry) / 8;
+// Behind it, on a line of its own: how many workgroups have come to run, and
+// whether the march goes.
+struct MarchGate {
+    unsigned arrived, verdict;
+};
+enum : unsigned { kGo = 1u, kNoGo = 2u };
+constexpr int kGateWord = 16, kEntryWords = kGateWord + (int)sizeof(MarchGate) / 8;
+static_assert(sizeof(MarchEntry) <= kGateWord * 8 && sizeof(MarchGate) == 8, "entry of a march");
+// Whether all n workgroups of a launch run at the same time, the same answer
+// in each; one thread of each asks.  The last to arrive lets the march go: the
+// others have arrived and wait here.  One that has looked `limit` times (about
+// 1 us each) without an answer calls it off, and those that come later find
+// that.  The verdict is set once, so no workgroup waits for one that does not
+// run, whatever else holds the CUs: other streams' kernels, or the workgroups
+// of other marches that wait in turn.
+__device__ __forceinline__ bool gather(MarchGate *g, unsigned n, int limit)
+{
+    unsigned is = 0u;
+    const unsigned before = __hip_atomic_fetch_add(&g->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + 1u == n && limit > 0)
+        __hip_atomic_compare_exchange_strong(&g->verdict, &is, kGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    for (int k = 0; k < limit; ++k) {
+        const unsigned v = __hip_atomic_load(&g->verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v != 0u) return v == kGo;
+    }
+    is = 0u;
+    __hip_atomic_compare_exchange_strong(&g->verdict, &is, kNoGo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    return is == kGo;  // what stood there, if anything did
+}
 // Clears the words before a march (step numbers start at 1) and forms its entry.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_open_march(LatticeDesc L, int64_t iter0, int64_t n)
@@ -646,7 +683,10 @@ __global__ __launch_bounds__(kBlock) void k_open_march(LatticeDesc L, int64_t it
     if (blockIdx.x == 0 && threadIdx.x < kWave) {
         const int slot = (int)((iter0 - L.iter0) % 3);
         const double bound = abar_of(L, slot, 0);
-        if (threadIdx.x == 0) *(MarchEntry *)(a + n) = {L.sc->t[slot], bound, L.sc->last_dt, L.sc->null_launches};
+        if (threadIdx.x == 0) {
+            *(MarchEntry *)(a + n) = {L.sc->t[slot], bound, L.sc->last_dt, L.sc->null_launches};
+            *(MarchGate *)(a + n + kGateWord) = {0u, 0u};
+        }
     }
 }
 
@@ -760,7 +800,12 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
         for (int v = 0; v < V; ++v) db[v] = has_bed ? ddiv<T>(br[v] - bl[v], T(2) * P.dx) : T(0);
     }
     MarchEntry at;
-    if constexpr (GRID) at = *(const MarchEntry *)((const unsigned long long *)L.u[0] + grid_march_words<SYS, T>(nblk));
+    MarchGate *gate = nullptr;
+    if constexpr (GRID) {
+        unsigned long long *o = (unsigned long long *)L.u[0] + grid_march_words<SYS, T>(nblk);
+        at = *(const MarchEntry *)o;
+        gate = (MarchGate *)(o + kGateWord);
+    }
     else at = {L.sc->t[n0 % 3], abar_of(L, (int)(n0 % 3), 0), L.sc->last_dt, L.sc->null_launches};
     double t = at.t, t_before = t, last_dt = at.last_dt;
     double ab = at.bound;
@@ -769,6 +814,12 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     unsigned long long bad = ~0ull;
     Coefs<T> cf0;
     coefs_of<D, T>(L, ab, 0.0, 0.0, cf0);
+    if constexpr (GRID) {  // nothing is written before this
+        __shared__ int go;
+        if (threadIdx.x == 0) go = gather(gate, (unsigned)nblk, L.gather_looks);
+        __syncthreads();
+        if (!go) return;
+    }
     int32_t s = 0;
     for (; s < nsteps; ++s) {
         const int64_t n = n0 + s;
@@ -963,14 +1014,16 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             bool ok = true;
             for (int j = lane; j < nblk; j += kWave) {
                 T other;
-                ok = hear<1>(o + (size_t)j * kBoundWords, &other, (unsigned)(s + 1)) && ok;
+                ok = hear<1>(o + (size_t)j * kBoundWords, &other, (unsigned)(s + 1), L.hear_looks) && ok;
                 got = other > got ? other : got;
             }
             T e[V][NV];
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 if (far[v] >= 0)
-                    ok = hear<NV>((unsigned long long *)L.u[set] + (size_t)far[v] * NV * kWords, e[v], (unsigned)(s + 1)) && ok;
+                    ok = hear<NV>((unsigned long long *)L.u[set] + (size_t)far[v] * NV * kWords, e[v],
+                                  (unsigned)(s + 1), L.hear_looks) &&
+                         ok;
             if (__ballot(!ok)) {  // a workgroup has not answered: give the run up
                 flags |= 1u;
                 if (bad == ~0ull) bad = (unsigned long long)n - null0;
@@ -1026,6 +1079,28 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             cur.v[0] = lane == 0 ? dbits(ab) : 0ull;
             cur.v[1] = cur.v[2] = nxt.v[0] = nxt.v[1] = nxt.v[2] = 0ull;
         }
+    }
+}
+
+// The steps of a march over several workgroups that was called off (gather), on
+// one workgroup that waits for nobody: the strips dealt to its waves, the
+// populations in memory between steps, as one launch per step leaves them.  The
+// strips of a wave follow one another (4096 cells of Euler FP32: 14.3 us per step
+// against 4.4 in one launch per step), which is the price of the rare launch that
+// did not find room on the device within some 60 ms.  Where the march went,
+// this launch ends at once.
+template <int SYS, typename T>
+__global__ __launch_bounds__(kStripWaves * kWave) void k_strips1d(LatticeDesc L, int64_t iter0, int32_t nsteps,
+                                                                 const MarchGate *gate)
+{
+    if (gate->verdict == kGo) return;
+    const int nw = (int)(blockDim.x >> 6), w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c0 = (int)((int64_t)w * L.ncols / nw), c1 = (int)((int64_t)(w + 1) * L.ncols / nw);
+    for (int s = 0; s < nsteps; ++s) {
+        if (c0 < c1) seg1d<SYS, T>(L, iter0 + s, c0, c1);
+        __threadfence();  // the step's stores and atomics, before the barrier, and none of them from an old line after it
+        __syncthreads();
+        __threadfence();
     }
 }
 

@@ -49,3 +49,82 @@ def test_launches_that_take_no_step(n, prec):
         assert a.sync() == b.sync() and np.array_equal(a.moments(), b.moments())
         a.close()
         b.close()
+
+
+def _problem(kind, n, face):
+    p = {"advection": lambda: W.advection_sine(n=n), "euler": lambda: W.euler_seeded_1d(3, n=n),
+         "swe": lambda: W.swe_bed_1d(n=n), "reactive": lambda: W.reactive_seeded_1d(1, n=n)}[kind]()
+    p.bc = (face,) * 4
+    return p
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("kind,face", [("advection", A.PERIODIC), ("euler", A.REFLECTIVE), ("swe", A.REFLECTIVE),
+                                       ("swe", A.TRANSMISSIVE), ("reactive", A.TRANSMISSIVE)])
+def test_launch_whose_workgroups_do_not_all_run(kind, face, prec):
+    """With no look at the others a launch calls its march off, and one
+    workgroup takes its steps: fewer strips than its waves, as many and more,
+    whole launches, time-targeted ones, and the march again after them."""
+    require_gpu()
+    for n in (697, 929, 1921, 4096):
+        p = _problem(kind, n, face)
+        say(f"[grid march, called off] {kind} face={face} prec={prec} {n} cells")
+        a, b = (gpu_lattice(p, prec, omega_export=True) for _ in range(2))
+        a.set_march_limits(gather_looks=0)
+        a.step(35)
+        for _ in range(35):
+            b.step(1)
+        sa, sb = a.sync(check=False), b.sync(check=False)
+        assert sa == sb and np.array_equal(a.moments(), b.moments()) and np.array_equal(a.omega(), b.omega()), n
+        k = a.step_until(sa["t"] + 40.5 * sa["last_dt"])
+        a.set_march_limits()
+        a.step(33)
+        for _ in range(k + 33):
+            b.step(1)
+        assert a.sync(check=False) == b.sync(check=False) and np.array_equal(a.moments(), b.moments()), n
+        a.close()
+        b.close()
+
+
+def test_march_limits_are_checked():
+    require_gpu()
+    L = gpu_lattice(_problem("euler", 4096, A.TRANSMISSIVE), A.F32)
+    for bad in ((-1, 1), (1, -1)):
+        with pytest.raises(A.ArlbmError) as e:
+            L.set_march_limits(*bad)
+        assert e.value.code == A.EINVAL
+    L.close()
+
+
+@pytest.mark.parametrize("n,prec", [(4096, A.F32), (4096, A.F64), (15000, A.F32)])
+def test_lattices_on_several_streams_run_side_by_side(n, prec):
+    """Four lattices on streams of their own take less than three times as
+    long as one of them: one after the other they would take four times."""
+    import time
+
+    import torch
+
+    require_gpu()
+    p = _problem("euler", n, A.TRANSMISSIVE)
+    lats = []
+    for _ in range(4):
+        L = A.Lattice(A.config_from(p, precision=prec), stream=torch.cuda.Stream())
+        L.set_state(p.U0)
+        lats.append(L)
+
+    def timed(some):
+        best = float("inf")
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for L in some:
+                L.step(1024)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        return best
+
+    one, four = timed(lats[:1]), timed(lats)
+    say(f"[grid march] {n} cells prec={prec}: one lattice {1e6 * one:.0f} us, four on four streams {1e6 * four:.0f} us")
+    assert four < 3.0 * one
+    for L in lats:
+        L.close()
