@@ -21,12 +21,13 @@ static_assert(strip_out_w(1) == kOutW && strip_out_w(2) == 120, "strip geometry"
 // kMarchWaves waves, of one cell per lane where 58 cells a wave hold the
 // lattice (Euler FP32 400 cells 1.67 against 1.70 us per step of two, 100 cells
 // 1.08 against 1.51), else, for advection, of two (1920 cells FP32 1.13 us,
-// FP64 1.73, against 1.94 and 2.55 over several workgroups).  Larger lattices
+// FP64 1.72, against 1.92 and 2.07 over several workgroups).  Larger lattices
 // march over several workgroups: for Euler and shallow water beyond 928 cells
-// (FP32 2.66 against 2.77 us there, FP64 3.86 against 3.75; two cells per lane
-// at 1500 cells 3.89 against 2.69), for the reactive system, bound by one CU's
-// kinetics, earlier (FP64 400 cells 5.6 against 5.5, 928 9.2 against 6.1; FP32
-// 600 3.8 against 3.9, 928 4.5 against 4.0).
+// (928 in one against 929 in several: Euler FP32 2.46 against 2.58 us, FP64 3.78
+// against 3.22, shallow water 1.98 against 2.22 and 3.16 against 2.90; two cells
+// per lane at 1500 cells 3.89), for the reactive system, bound by one CU's
+// kinetics, earlier (FP64 406 cells 4.90 against 5.11 for 407, 928 9.2 against
+// 5.8; FP32 696 3.51 against 3.56, 928 4.5 against 3.6).
 constexpr int kMarchWaves = 16;
 __host__ __device__ constexpr int march_width(int64_t nx) { return nx <= kMarchWaves * strip_out_w(1) ? 1 : 2; }
 constexpr int march_cells(int system, bool f64)
@@ -36,17 +37,21 @@ constexpr int march_cells(int system, bool f64)
 // Several workgroups: four waves each (one per SIMD), and at most a quarter of
 // what the device holds at once (kGridShare), so that the lattices of several
 // streams, of which a process runs four at a time by default, find room beside
-// each other: FP32 74240 cells (reactive 59392), FP64 37120 (reactive 29696).
-// The exchange grows
-// with their number (us per step, one launch per step against the march: Euler
-// FP32 14800 cells 4.54 / 3.11, 40000 4.72 / 4.18, 100000 5.53 / 5.23, 118000
-// 5.61 / 5.58; FP64 14800 5.30 / 4.10, 29000 5.41 / 4.84, 40000 5.59 / 5.42,
-// 50000 5.62 / 5.89), which sets the largest lattices.
+// each other; the reactive system's registers set the sizes.  us per step and
+// lattice, one launch per step against the march, for one lattice: Euler FP32
+// 4096 cells 4.54 / 2.58, 29000 4.60 / 2.92, 59392 4.75 / 3.36, FP64 4096 5.11 /
+// 3.48, 29696 5.36 / 3.99; for two, each on a stream and host thread of its
+// own: FP32 29000 2.48 / 1.89, 58000 2.64 / 2.41, FP64 29000 3.03 / 2.44; for
+// four, whose workgroups share the CUs and wait for one another's slowest: FP32
+// 14800 1.32 / 1.00, 29000 1.41 / 1.31, 37000 1.46 / 1.54, 45000 1.51 / 1.68,
+// FP64 9500 1.51 / 1.33, 19000 1.62 / 1.62, 29000 1.71 / 2.06.  So one or two
+// lattices gain over the whole range, three up to three quarters of it and four
+// up to about two thirds, and the largest sizes are drawn for one or two.
 constexpr int kGridWaves = 4, kGridShare = 4;
-constexpr int64_t grid_march_cells(bool f64) { return (int64_t)(f64 ? 160 : 320) * kGridWaves * kOutW; }
-// Steps from which the several workgroups pay for their launch (us for 16 / 32
-// steps of 4096 Euler cells, one launch per step against one: FP32 82 / 149
-// against 79 / 123, FP64 90 / 172 against 96 / 158).
+constexpr int64_t grid_march_cells(bool f64) { return (int64_t)(f64 ? 128 : 256) * kGridWaves * kOutW; }
+// Steps from which the several workgroups pay for their three launches (us per
+// step in calls of 32, against one launch per step: Euler FP32 4096 cells 2.85
+// against 4.38, 58000 3.70 against 4.61, FP64 4096 3.76 against 4.93).
 constexpr int kGridMinSteps = 32;
 // Looks of about 1 us at the words of other workgroups before one calls a march
 // off (60 ms, in which other work on the device lets the rest come to run) or,

@@ -555,13 +555,18 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // promise it, but those of a process run one after the other on one queue of
 // the device, which the caller's stream waits for and which waits for that:
 // four 4096-cell Euler lattices on streams of their own took 2.9 us per step
-// and lattice FP32, 4.1 FP64, and so take 0.8 and 1.2; one lattice 40 steps at a
-// time 3.5-6.5, so 3.2.)  A workgroup's outer cells and its bound
+// and lattice FP32, 4.1 FP64, and so take 0.8 and 1.1; one lattice 40 steps at a
+// time 3.5-6.5, so 2.8.)  A workgroup's outer cells and its bound
 // go to the others through memory, in the two moment buffers in turn (in 1D
 // they serve the read-back only), each word carrying its step's number, so
 // that no fence and no grid barrier is needed.  A set is rewritten two steps
-// later, by a workgroup that has heard every bound of the step between, which
-// is told only after its teller has read all it needs of the set.
+// later, behind the barriers of a workgroup that has heard every bound of the
+// step between, which is told only behind the barrier that its teller's waves
+// pass when they have read all they need of the set.  A step's second barrier
+// lets the waves of a workgroup share what they wait for: while each of them
+// looked for every bound, the looks of several lattices at once got in each
+// other's way (36000 cells of Euler, four lattices: FP32 2.08 -> 1.50 us per
+// step and lattice, FP64 3.48 -> 2.40; 14800 FP64 1.9 -> 1.4).
 // What bounds a step: the dependent chain of one wave (LDS read, bound
 // reduction, FP64 time step, indicator, collision, LDS write, barrier) while
 // every SIMD has one wave (up to 232 cells), one CU's instruction issue above.
@@ -570,9 +575,9 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // 2.38 -> 0.78, Euler FP32 928 4.45 -> 2.66, FP64 6.61 -> 3.86, shallow water
 // FP64 600 4.81 -> 2.82, reactive FP64 256 7.84 -> 5.36; two cells per lane at
 // 1920 cells: advection FP32 4.06 -> 1.13.  GRID against one launch per step
-// (about 1.2 us of a step are the exchange): 4096 cells Euler FP32 4.33 ->
-// 2.88, FP64 4.91 -> 3.92, shallow water FP32 4.43 -> 2.61, reactive FP64 7.14
-// -> 6.23, advection FP32 3.94 -> 1.90; 14800 cells Euler FP32 4.33 -> 3.13.
+// (about 1 us of a step is the exchange): 4096 cells Euler FP32 4.54 -> 2.58,
+// FP64 5.11 -> 3.48, shallow water FP32 4.33 -> 2.55, reactive FP64 7.47 -> 6.09,
+// advection FP32 3.90 -> 1.88; 14800 cells Euler FP32 4.52 -> 2.69.
 template <int SYS>
 __host__ __device__ constexpr int march_values()
 {
@@ -698,6 +703,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     constexpr int kWords = kTellWords<T>;
     __shared__ T edge[2][kMarchWaves][2 * kHalo][NV];
     __shared__ T bound[2][kMarchWaves];
+    __shared__ T heard[GRID ? kGridWaves : 1];
     const int blk = GRID ? (int)blockIdx.x : 0, nblk = GRID ? (int)gridDim.x : 1;
     const int lane = (int)(threadIdx.x & (kWave - 1)), wave = (int)(threadIdx.x >> 6);
     const int bw = (int)(blockDim.x >> 6), nw = GRID ? bw * nblk : bw, nx = L.nx;
@@ -1006,30 +1012,41 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
         m = max_step<0x114, 0xf>(m);
         m = max_step<0x118, 0xf>(m);
         if constexpr (GRID) {
-            // every workgroup's bound: lane i hears workgroups i, i + 64, ..
+            // The first and the last wave hear the cells outside, the two between
+            // them every workgroup's bound, a lane each, and tell it the others
+            // through LDS: words looked for once per workgroup, not by every wave.
             unsigned long long *o = (unsigned long long *)L.u[set] + (size_t)nblk * 2 * kHalo * NV * kWords;
             const T mine = read_lane(m, kMarchWaves - 1);
             if (wave == 0 && lane == 0) tell(o + (size_t)blk * kBoundWords, mine, (unsigned)(s + 1));
             T got = mine;
             bool ok = true;
-            for (int j = lane; j < nblk; j += kWave) {
-                T other;
-                ok = hear<1>(o + (size_t)j * kBoundWords, &other, (unsigned)(s + 1), L.hear_looks) && ok;
-                got = other > got ? other : got;
-            }
             T e[V][NV];
+            if (wave == 0 || wave == bw - 1) {
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                if (far[v] >= 0)
-                    ok = hear<NV>((unsigned long long *)L.u[set] + (size_t)far[v] * NV * kWords, e[v],
-                                  (unsigned)(s + 1), L.hear_looks) &&
-                         ok;
-            if (__ballot(!ok)) {  // a workgroup has not answered: give the run up
+                for (int v = 0; v < V; ++v)
+                    if (far[v] >= 0)
+                        ok = hear<NV>((unsigned long long *)L.u[set] + (size_t)far[v] * NV * kWords, e[v],
+                                      (unsigned)(s + 1), L.hear_looks) &&
+                             ok;
+            } else {
+                for (int j = (wave - 1) * kWave + lane; j < nblk; j += (bw - 2) * kWave) {
+                    T other;
+                    ok = hear<1>(o + (size_t)j * kBoundWords, &other, (unsigned)(s + 1), L.hear_looks) && ok;
+                    got = other > got ? other : got;
+                }
+                got = wave_max<T>(got);
+            }
+            if (__ballot(!ok)) got = T(__builtin_huge_val());  // a workgroup has not answered
+            if (lane == 0) heard[wave] = got;
+            __syncthreads();
+            ab = 0.0;
+#pragma unroll
+            for (int i = 0; i < kGridWaves; ++i) ab = (double)heard[i] > ab ? (double)heard[i] : ab;
+            if (ab > 1.0e300) {  // the whole workgroup gives the run up
                 flags |= 1u;
                 if (bad == ~0ull) bad = (unsigned long long)n - null0;
                 break;
             }
-            ab = (double)wave_max<T>(got);
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 if (far[v] >= 0) take(v, e[v]);

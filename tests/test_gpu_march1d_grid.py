@@ -128,3 +128,22 @@ def test_lattices_on_several_streams_run_side_by_side(n, prec):
     assert four < 3.0 * one
     for L in lats:
         L.close()
+
+
+@pytest.mark.parametrize("prec,sizes", [(A.F32, (14848, 14849, 29697, 59392, 59393)), (A.F64, (14849, 29696, 29697))])
+@pytest.mark.parametrize("kind,face", [("advection", A.PERIODIC), ("euler", A.PERIODIC), ("reactive", A.REFLECTIVE)])
+def test_bounds_of_many_workgroups(kind, face, prec, sizes):
+    """As many workgroups as a wave has lanes, one more, more than the lanes of
+    the two waves that hear their bounds, and the last size of the march and
+    the first beyond it."""
+    require_gpu()
+    for n in sizes:
+        p = _problem(kind, n, face)
+        say(f"[grid march, many workgroups] {kind} face={face} prec={prec} {n} cells")
+        a, b = (gpu_lattice(p, prec) for _ in range(2))
+        a.step(33)
+        for _ in range(33):
+            b.step(1)
+        assert a.sync(check=False) == b.sync(check=False) and np.array_equal(a.moments(), b.moments()), n
+        a.close()
+        b.close()
