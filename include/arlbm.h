@@ -73,6 +73,7 @@ enum { ARLBM_OMEGA_ADAPTIVE = 0, ARLBM_OMEGA_FIXED = 1 };
 #define ARLBM_FLAG_NONFINITE 1u
 #define ARLBM_FLAG_POSITIVITY 2u
 #define ARLBM_FLAG_DEGENERATE 4u
+#define ARLBM_FLAG_STALLED 8u  /* a 1D launch of several workgroups was given up */
 
 typedef struct arlbm_config {
     int32_t abi_version;  /* ARLBM_ABI_VERSION                                  */
@@ -179,7 +180,8 @@ int arlbm_step(arlbm_lattice *h, int64_t n);
  * same time before they call it off; one workgroup then takes the steps, with
  * the same results but slower (0: always).  hear_looks (2^24): how long a
  * workgroup waits for another's words of a step, once all run, before it
- * gives up.  The calls that step h after this one use them. */
+ * gives up; the lattice is then STALLED until its state is set or loaded
+ * again.  The calls that step h after this one use them. */
 int arlbm_set_march_limits(arlbm_lattice *h, int32_t gather_looks, int32_t hear_looks);
 
 /* Whole steps until the simulated time reaches t_final (t >= t_final; the
@@ -192,10 +194,10 @@ int arlbm_step_until(arlbm_lattice *h, double t_final, int64_t max_steps, int64_
 
 /* Wait for the stream and report the status.  Returns ENONFINITE,
  * EDEGENERATE or EPOSITIVITY when the matching flag is set (status still
- * filled), else 0.  EPOSITIVITY is advisory: the method has no positivity
- * mechanism, so a state with a density, pressure or depth below its floor is
- * still the method's result and stepping may continue; the two others mean
- * the state is no longer usable. */
+ * filled), EDEVICE for STALLED, else 0.  EPOSITIVITY is advisory: the method
+ * has no positivity mechanism, so a state with a density, pressure or depth
+ * below its floor is still the method's result and stepping may continue; the
+ * others mean the state is no longer usable. */
 int arlbm_sync(arlbm_lattice *h, arlbm_status *st);
 
 /* Copy the current moments U = sum_k f_k to host FP64 planes (synchronises;

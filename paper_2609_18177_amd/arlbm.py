@@ -25,7 +25,7 @@ ABI_VERSION = 4
 
 OK, EINVAL, ENOMEM, EDEVICE, ENONFINITE, EPOSITIVITY, EDEGENERATE, EBUSY, EBUDGET = \
     0, -1, -2, -3, -4, -5, -6, -7, -8
-FLAG_NONFINITE, FLAG_POSITIVITY, FLAG_DEGENERATE = 1, 2, 4
+FLAG_NONFINITE, FLAG_POSITIVITY, FLAG_DEGENERATE, FLAG_STALLED = 1, 2, 4, 8
 
 
 class ArlbmError(RuntimeError):

@@ -873,7 +873,7 @@ extern "C" int arlbm_step_until(arlbm_lattice *h, double t_final, int64_t max_st
     while (real < max_steps) {
         const double t = sc.t[h->step % 3];
         if (t >= t_final) break;
-        if (sc.flags & (ARLBM_FLAG_NONFINITE | ARLBM_FLAG_DEGENERATE)) break;
+        if (sc.flags & (ARLBM_FLAG_NONFINITE | ARLBM_FLAG_DEGENERATE | ARLBM_FLAG_STALLED)) break;
         // launch the estimated remaining steps plus one; a launch that finds
         // the state at or past t_final leaves it unchanged, so the surplus
         // costs one copy of the populations and the result does not depend
@@ -925,6 +925,8 @@ extern "C" int arlbm_sync(arlbm_lattice *h, arlbm_status *st)
         st->flags = sc.flags;
         st->first_bad_step = sc.first_bad_step == ~0ull ? -1 : (int64_t)sc.first_bad_step;
     }
+    if (sc.flags & ARLBM_FLAG_STALLED)
+        return fail(h, ARLBM_EDEVICE, "the workgroups of a 1D launch did not hear from one another: the steps were given up");
     if (sc.flags & ARLBM_FLAG_NONFINITE) return fail(h, ARLBM_ENONFINITE, "a moment became non-finite");
     if (sc.flags & ARLBM_FLAG_DEGENERATE) return fail(h, ARLBM_EDEGENERATE, "sum of wave-speed bounds became zero");
     if (sc.flags & ARLBM_FLAG_POSITIVITY) return fail(h, ARLBM_EPOSITIVITY, "a density, pressure or depth fell below its floor");

@@ -602,7 +602,7 @@ __device__ __forceinline__ void tell(unsigned long long *o, T v, unsigned tag)
 }
 // N values of the step `tag`; false when they have not come after `limit`
 // looks, some ten seconds (the writers run, and a step takes microseconds; the
-// limit only makes the end certain).
+// limit only makes the end certain, and a march it ends is reported as such).
 template <int N, typename T>
 __device__ __forceinline__ bool hear(unsigned long long *o, T *v, unsigned tag, int limit)
 {
@@ -653,6 +653,7 @@ struct MarchGate {
     unsigned arrived, verdict;
 };
 enum : unsigned { kGo = 1u, kNoGo = 2u };
+constexpr unsigned kStalled = 8u;  // status flag of a march that was given up (ARLBM_FLAG_STALLED)
 constexpr int kGateWord = 16, kEntryWords = kGateWord + (int)sizeof(MarchGate) / 8;
 static_assert(sizeof(MarchEntry) <= kGateWord * 8 && sizeof(MarchGate) == 8, "entry of a march");
 // Whether all n workgroups of a launch run at the same time, the same answer
@@ -1042,8 +1043,10 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             ab = 0.0;
 #pragma unroll
             for (int i = 0; i < kGridWaves; ++i) ab = (double)heard[i] > ab ? (double)heard[i] : ab;
-            if (ab > 1.0e300) {  // the whole workgroup gives the run up
-                flags |= 1u;
+            if (ab == __builtin_huge_val()) {  // (no wave's own bound is: those are finite)
+                // the whole workgroup gives the run up behind this step; the
+                // others then wait for it in vain and do too
+                flags |= kStalled;
                 if (bad == ~0ull) bad = (unsigned long long)n - null0;
                 break;
             }
@@ -1076,7 +1079,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             for (int k = 0; k < Q; ++k)
 #pragma unroll
                 for (int c = 0; c < M; ++c) sto(fout + (size_t)(k * M + c) * L.pstride, (unsigned)x[v], f[v][k][c]);
-    unsigned any = flags & 4u;
+    unsigned any = flags & (4u | kStalled);
     if (__ballot((flags & 1u) != 0u)) any |= 1u;
     if (__ballot((flags & 2u) != 0u)) any |= 2u;
     DevScalars *so = L.sc;
@@ -1089,7 +1092,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             so->t[(ne + 2) % 3] = s == nsteps ? t_before : t;
             so->t[ne % 3] = t;
             so->last_dt = last_dt;
-            so->null_launches = null0 + (any & 4u ? 0ull : (unsigned long long)(nsteps - s));
+            so->null_launches = null0 + (any & (4u | kStalled) ? 0ull : (unsigned long long)(nsteps - s));
         }
         if (lane <= abar_mask(L)) {
             AbarCopy &cur = so->abar[ne % 3][lane], &nxt = so->abar[(ne + 1) % 3][lane];

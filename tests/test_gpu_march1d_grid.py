@@ -147,3 +147,35 @@ def test_bounds_of_many_workgroups(kind, face, prec, sizes):
         assert a.sync(check=False) == b.sync(check=False) and np.array_equal(a.moments(), b.moments()), n
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("n", [929, 4096, 15000])
+def test_march_that_is_given_up(n, prec):
+    """With no look at what the others wrote every workgroup gives up behind
+    its first step: a status and an error of its own, not a non-finite state;
+    the steps that were not taken are not steps at the stop time; and a state
+    set again is stepped as ever."""
+    require_gpu()
+    p = _problem("euler", n, A.TRANSMISSIVE)
+    say(f"[grid march, given up] {n} cells prec={prec}")
+    L = gpu_lattice(p, prec)
+    L.step(3)
+    L.set_march_limits(hear_looks=0)
+    L.step(40)
+    st = L.sync(check=False)
+    assert st["rc"] == A.EDEVICE and st["flags"] == A.FLAG_STALLED and st["first_bad_step"] == 3, st
+    assert st["step"] == 43
+    with pytest.raises(A.ArlbmError) as e:
+        L.sync()
+    assert e.value.code == A.EDEVICE
+    assert L.step_until(2.0 * st["t"] + 1.0) == 0  # not stepped on
+    L.set_march_limits()
+    L.set_state(p.U0)
+    ref = gpu_lattice(p, prec)
+    L.step(40)
+    for _ in range(40):
+        ref.step(1)
+    assert L.sync() == ref.sync() and np.array_equal(L.moments(), ref.moments())
+    L.close()
+    ref.close()
