@@ -2087,6 +2087,7 @@ int finish_staged(arlbm_server *s)
             d.c.flags = sc.flags;
             d.c.first_bad_step = sc.first_bad_step == ~0ull ? -1 : (int64_t)sc.first_bad_step;
             int rc = e != hipSuccess ? ARLBM_EDEVICE : ARLBM_OK;
+            if (rc == ARLBM_OK && (sc.flags & ARLBM_FLAG_STALLED)) rc = ARLBM_EDEVICE;
             if (rc == ARLBM_OK && (sc.flags & ARLBM_FLAG_NONFINITE)) rc = ARLBM_ENONFINITE;
             if (rc == ARLBM_OK && (sc.flags & ARLBM_FLAG_DEGENERATE)) rc = ARLBM_EDEGENERATE;
             // the positivity flag is advisory: the moments are still the result
@@ -2149,7 +2150,7 @@ void take_gathers(arlbm_server *s)
     for (auto &g : s->gather) {
         if (!g.pending || hipEventQuery(g.ev) != hipSuccess) continue;
         for (size_t i = 0; i < g.ids.size(); ++i)
-            if (g.host[i] & (ARLBM_FLAG_NONFINITE | ARLBM_FLAG_DEGENERATE)) s->failing.push_back(g.ids[i]);
+            if (g.host[i] & (ARLBM_FLAG_NONFINITE | ARLBM_FLAG_DEGENERATE | ARLBM_FLAG_STALLED)) s->failing.push_back(g.ids[i]);
         g.pending = false;
     }
 }

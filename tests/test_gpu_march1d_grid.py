@@ -179,3 +179,27 @@ def test_march_that_is_given_up(n, prec):
     assert L.sync() == ref.sync() and np.array_equal(L.moments(), ref.moments())
     L.close()
     ref.close()
+
+
+def test_state_of_a_given_up_march_in_a_server():
+    """A saved state of a march that was given up leaves a server's mix early,
+    with the same error."""
+    require_gpu()
+    p = _problem("euler", 4096, A.TRANSMISSIVE)
+    L = gpu_lattice(p, A.F32)
+    L.set_march_limits(hear_looks=0)
+    L.step(40)
+    blob = L.save_state()
+    L.close()
+    srv = A.Server(1 << 28, A.F32)
+    rid = srv.submit_state(A.config_from(p, precision=A.F32), blob, 2000)
+    done = []
+    for _ in range(4000):
+        srv.iterate()
+        done = srv.poll(4)
+        if done:
+            break
+    srv.close()
+    say("[grid march, given up] served:", done)
+    assert done[0]["id"] == rid and done[0]["status"] == A.EDEVICE and done[0]["steps"] < 100
+    assert done[0]["flags"] & A.FLAG_STALLED and done[0]["U"] is None
