@@ -170,8 +170,9 @@ int arlbm_set_state_device(arlbm_lattice *h, const double *U0_dev, const double 
  * trip): one kernel launch per step in 2D and 3D; in 1D one launch takes up to
  * 1024 steps where the lattice fits the device's registers (above 928 cells
  * or so by workgroups that exchange words through the two moment buffers, for
- * 32 steps and more, and not on a stream under capture).  Device-side problems
- * are latched in the status flags and reported by arlbm_sync. */
+ * 32 steps and more, and not on a stream under capture; the calls that read
+ * or save the state form the moments there anew).  Device-side problems are
+ * latched in the status flags and reported by arlbm_sync. */
 int arlbm_step(arlbm_lattice *h, int64_t n);
 
 /* Limits of the waits of a 1D launch of several workgroups, in looks of about

@@ -1093,6 +1093,8 @@ extern "C" int arlbm_save_state(arlbm_lattice *h, void *blob, size_t bytes)
     int rc = arlbm_state_bytes(h, &need);
     if (rc) return rc;
     if (!blob || bytes < need) return fail(h, ARLBM_EINVAL, "state buffer too small");
+    // (the march of 1D lattices leaves the words its workgroups exchanged there)
+    if (h->cfg.dim == 1 && (rc = form_moments(h)) != ARLBM_OK) return rc;
     StateHeader hd{kMagic, h->cfg.precision, h->desc.variant, h->desc.nx, h->desc.ny, h->desc.nz, 0, h->step,
                    h->sz.f_bytes,
                    h->sz.u_bytes};

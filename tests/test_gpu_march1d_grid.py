@@ -203,3 +203,30 @@ def test_state_of_a_given_up_march_in_a_server():
     say("[grid march, given up] served:", done)
     assert done[0]["id"] == rid and done[0]["status"] == A.EDEVICE and done[0]["steps"] < 100
     assert done[0]["flags"] & A.FLAG_STALLED and done[0]["U"] is None
+
+
+@pytest.mark.parametrize("prec", [A.F32, A.F64])
+@pytest.mark.parametrize("kind,n", [("euler", 600), ("euler", 4096), ("swe", 2000), ("reactive", 1000)])
+def test_saved_state_holds_the_moments(kind, n, prec):
+    """The moment planes of a saved state are the moments of its populations,
+    however the steps before it were launched."""
+    require_gpu()
+    p = _problem(kind, n, A.TRANSMISSIVE)
+    a, b = (gpu_lattice(p, prec) for _ in range(2))
+    a.step(40)
+    for _ in range(40):
+        b.step(1)
+    real, stride = (np.float32 if prec == A.F32 else np.float64), (n + 63) // 64 * 64 + 1088
+
+    def planes(L):
+        blob, f = L.save_state(), int(L.sizes.f_bytes)
+        fp = np.frombuffer(blob, dtype=real, count=L.q * L.m * stride, offset=56).reshape(L.q * L.m, stride)[:, :n]
+        up = np.frombuffer(blob, dtype=real, count=L.m * stride, offset=56 + f).reshape(L.m, stride)[:, :n]
+        return blob[:56], fp, up
+
+    (ha, fa, ua), (hb, fb, ub) = planes(a), planes(b)
+    say(f"[saved 1d state] {kind} {n} cells prec={prec}")
+    assert ha == hb and np.array_equal(fa, fb) and np.array_equal(ua, ub)
+    assert np.array_equal(ua.astype(np.float64), a.moments())
+    a.close()
+    b.close()
