@@ -875,21 +875,23 @@ extern "C" int arlbm_step_until(arlbm_lattice *h, double t_final, int64_t max_st
         if (t >= t_final) break;
         if (sc.flags & (ARLBM_FLAG_NONFINITE | ARLBM_FLAG_DEGENERATE | ARLBM_FLAG_STALLED)) break;
         // launch the estimated remaining steps plus one; a launch that finds
-        // the state at or past t_final leaves it unchanged, so the surplus
-        // costs one copy of the populations and the result does not depend
-        // on the estimate.  Before the first step the estimate takes the
-        // wave-speed bounds of the initial state.  A march of one workgroup
-        // ends at t_final whatever its length, so the surplus costs nothing
-        // there, and half as many steps again save the round trips (25 us
-        // each) that a shrinking step would take (600 cells of FP64
-        // shallow water to t = 0.12: 1025 -> 1000 us).
-        const int slot = (int)(h->step % 3);
-        const double sa = (abar_host(sc, slot, 0) + (h->cfg.dim >= 2 ? abar_host(sc, slot, 1) : 0.0)) +
-                          (h->cfg.dim == 3 ? abar_host(sc, slot, 2) : 0.0);
+        // the state at or past t_final leaves it unchanged, so the result does
+        // not depend on the estimate.  Where every step is a launch, each of
+        // the surplus copies the populations, and the first estimate waits for
+        // a trial step: the time step of a point blast grows threefold in its
+        // first steps, by 1.3 in the first (96^2 Euler, a cell at pressure 10,
+        // to the time of 300 steps: 944 launches from the initial bounds, 715
+        // from the trial step's).  A march ends at t_final whatever its
+        // length, so there the surplus costs next to nothing and the bounds of
+        // the present state serve at once; in one workgroup half as many steps
+        // again save the round trips (25 us each) that a shrinking step would
+        // take (600 cells of FP64 shallow water to t = 0.12: 1025 -> 1000 us).
+        const bool one = h->cfg.dim == 1 && h->cfg.nx <= march_cells(h->cfg.system, is_f64(h));
+        const bool march = one || (h->cfg.dim == 1 && h->cfg.nx <= grid_march_cells(is_f64(h)));
+        const double sa = march ? abar_host(sc, (int)(h->step % 3), 0) : 0.0;
         const double dt = sa > 0.0 ? h->cfg.cfl * h->desc.dx / sa : sc.last_dt;
         double est = dt > 0.0 ? (t_final - t) / dt : 1.0;
-        if (h->cfg.dim == 1 && h->cfg.nx <= march_cells(h->cfg.system, is_f64(h)))
-            est += std::min(0.5 * est, (double)kMarchRun);
+        if (one) est += std::min(0.5 * est, (double)kMarchRun);
         int64_t k = est < 1e15 ? (int64_t)std::ceil(est) + 1 : 1;
         if (k > max_steps - real) k = max_steps - real;
         const hipError_t e = enqueue_steps(h, k);
