@@ -347,8 +347,8 @@ int arlbm_server_destroy(arlbm_server *s);
 /* The batched launch's work list for lattices of configurations cfgs[0..n-1]
  * served together (3D lattices, which run launches of their own, take no
  * part; neither do 2D lattices while they are so few and small that the
- * server steps each in a launch of tiles, which this list does not show), for
- * a launch of at most `waves` waves, computed on the host as the
+ * server steps each in a launch of tiles, which this list does not show but
+ * arlbm_plan_tiles does), for a launch of at most `waves` waves, computed on the host as the
  * server computes it (no GPU needed).  On return the list has *nsegs items
  * and the launch *nwaves waves; item k is segs[4k .. 4k+3] = (lattice index,
  * strip, first row, end row) for a 2D lattice, (lattice index, first strip,
@@ -359,6 +359,16 @@ int arlbm_server_destroy(arlbm_server *s);
  * (4 max_segs entries) is too small (the counts are still set). */
 int arlbm_plan_schedule(const arlbm_config *cfgs, int32_t n, int32_t waves, int32_t *queue_start,
                         int32_t *segs, int32_t max_segs, int32_t *nsegs, int32_t *nwaves);
+
+/* Which lattices of configurations cfgs[0..n-1] a device of cus CUs (256 on an
+ * MI355X) steps in tiles (one workgroup per tile of a small lattice) instead
+ * of in marching strips or planes, computed on the host as the library
+ * computes it (no GPU needed).  alone[i]: the tile's height, halo rows
+ * included, in 2D, its cells in z in 3D, for arlbm_step; served[i]: the same
+ * in a server that holds exactly these lattices, where a 2D lattice with a 0
+ * is stepped by the batched launch (arlbm_plan_schedule).  0: in no tiles.
+ * EINVAL on a bad configuration or argument. */
+int arlbm_plan_tiles(const arlbm_config *cfgs, int32_t n, int32_t cus, int32_t *alone, int32_t *served);
 
 /* How the server splits lattices of configurations cfgs[0..n-1] served
  * together into batched launches of at most `waves` waves, computed on the

@@ -119,6 +119,8 @@ def lib():
             "arlbm_plan_schedule": ([C.POINTER(Config), C.c_int32, C.c_int32, C.POINTER(C.c_int32),
                                      C.POINTER(C.c_int32), C.c_int32, C.POINTER(C.c_int32),
                                      C.POINTER(C.c_int32)], C.c_int),
+            "arlbm_plan_tiles": ([C.POINTER(Config), C.c_int32, C.c_int32, C.POINTER(C.c_int32),
+                                  C.POINTER(C.c_int32)], C.c_int),
             "arlbm_plan_groups": ([C.POINTER(Config), C.c_int32, C.c_int32, C.POINTER(C.c_int32),
                                    C.POINTER(C.c_int32)], C.c_int),
             "arlbm_kernel_exp": ([C.c_double], C.c_double),
@@ -430,6 +432,17 @@ def plan_schedule(cfgs, waves: int):
     _check(lib().arlbm_plan_schedule(arr, len(cfgs), int(waves), ip(qs), ip(sg), ns.value, C.byref(ns),
                                      C.byref(nw)))
     return qs, sg[:4 * ns.value].reshape(-1, 4), nw.value
+
+
+def plan_tiles(cfgs, cus: int = 256):
+    """The tile heights (2D: rows, 3D: cells in z) with which a device of cus
+    CUs steps these configurations, each alone and all served together (host
+    only); 0: in no tiles."""
+    arr = (Config * max(len(cfgs), 1))(*cfgs)
+    alone, served = (np.zeros(max(len(cfgs), 1), dtype=np.int32) for _ in range(2))
+    ip = lambda a: a.ctypes.data_as(C.POINTER(C.c_int32))  # noqa: E731
+    _check(lib().arlbm_plan_tiles(arr, len(cfgs), int(cus), ip(alone), ip(served)))
+    return alone[:len(cfgs)], served[:len(cfgs)]
 
 
 def plan_groups(cfgs, waves: int):

@@ -59,6 +59,27 @@ constexpr int kGridMinSteps = 32;
 constexpr int kGatherLooks = 1 << 16, kHearLooks = 1 << 24;
 constexpr int kStripWaves = 16;           // waves of k_strips1d
 constexpr int kMaxTileRows = 16;          // rows (waves) of a tile of the tiled 2D step
+// The tiled 3D step of small lattices (tile3d.hpp): tiles of kTile3X x kTile3Y
+// x tile3_z cells, or, where those fit one round of the CUs, of 4 cells in z.
+constexpr int kTile3X = 8, kTile3Y = 8;
+__host__ __device__ constexpr int tile3_z(int system, bool f64) { return system == 3 && f64 ? 4 : 8; }
+constexpr int64_t tiles3(int64_t nx, int64_t ny, int64_t nz, int64_t tz)
+{
+    return ((nx + kTile3X - 1) / kTile3X) * ((ny + kTile3Y - 1) / kTile3Y) * ((nz + tz - 1) / tz);
+}
+// Tiles per CU up to which the tiles beat the march, whose workgroups take as
+// long for a small lattice as for one of their own size: Euler FP32 64^3 (2
+// tiles per CU) 32 against 81 us, 96^3 (6.75) 107 against 91, FP64 61 / 162
+// and 246 / 193; advection 96^3 25 / 31 and 128^3 (16) 50 / 51, FP64 39 / 46
+// and 78 / 80.
+constexpr int kTiles3PerCu = 5, kTiles3PerCuAdv = 16;
+// Cells in z of a lattice's tiles, 0 where it marches through planes.
+constexpr int choose_tile_z(int system, bool f64, int64_t nx, int64_t ny, int64_t nz, int64_t cus)
+{
+    if (tiles3(nx, ny, nz, 4) <= cus) return 4;
+    const int tz = tile3_z(system, f64);
+    return tiles3(nx, ny, nz, tz) <= cus * (system == 0 ? kTiles3PerCuAdv : kTiles3PerCu) ? tz : 0;
+}
 constexpr int kBlock = 256;               // 4 independent waves per block
 constexpr int kWavesPerBlock = kBlock / kWave;
 

@@ -80,19 +80,17 @@ static hipError_t step_impl(const LatticeDesc &h, int64_t iter, hipStream_t s)
         // a small lattice in x-y-z tiles (tile3d.hpp), in the lower ones where
         // they fit one round of the CUs
         const int cus = num_cus();
-        auto tiles = [&](int tz) { return (int64_t)((h.nx + 7) / 8) * ((h.ny + 7) / 8) * ((h.nz + tz - 1) / tz); };
-        const int ntx = (h.nx + 7) / 8, nty = (h.ny + 7) / 8;
-        using B = Block3<SYS, real, false>;
-        if (tiles(4) <= cus) {
-            const int nwork = (int)tiles(4);
-            hipLaunchKernelGGL((k_tile3d<SYS, real, true>), dim3(grid_for(nwork, 1)), dim3(B::kThreads), 0, s, h, iter,
-                               ntx, nty, nwork);
-            return hipGetLastError();
-        }
-        if (tiles(B::TZ) <= (int64_t)cus * (SYS == 0 ? kTiles3PerCuAdv : kTiles3PerCu)) {
-            const int nwork = (int)tiles(B::TZ);
-            hipLaunchKernelGGL((k_tile3d<SYS, real, false>), dim3(grid_for(nwork, 1)), dim3(B::kThreads), 0, s, h,
-                               iter, ntx, nty, nwork);
+        const int tz = choose_tile_z(SYS, sizeof(real) == 8, h.nx, h.ny, h.nz, cus);
+        if (tz > 0) {
+            const int ntx = (h.nx + kTile3X - 1) / kTile3X, nty = (h.ny + kTile3Y - 1) / kTile3Y;
+            const int nwork = (int)tiles3(h.nx, h.ny, h.nz, tz);
+            constexpr int kThreads = Block3<SYS, real, false>::kThreads;
+            if (nwork <= cus && tz == 4)
+                hipLaunchKernelGGL((k_tile3d<SYS, real, true>), dim3(grid_for(nwork, 1)), dim3(kThreads), 0, s, h,
+                                   iter, ntx, nty, nwork);
+            else
+                hipLaunchKernelGGL((k_tile3d<SYS, real, false>), dim3(grid_for(nwork, 1)), dim3(kThreads), 0, s, h,
+                                   iter, ntx, nty, nwork);
             return hipGetLastError();
         }
         // one fused pass: tiles x plane chunks filling the chip once

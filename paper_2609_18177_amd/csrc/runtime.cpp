@@ -1796,7 +1796,7 @@ SchedLattice sched_lattice(int32_t i, const LatticeDesc &d, bool f64)
 // Euler lattice FP32 21.1 -> 9.2, FP64 34.9 -> 12.2, two of them 21.6 -> 17.8
 // and 35.8 -> 25.0 (three are past the line: batched 22.6 and 36.3), one beside
 // a 20000-cell 1D lattice 21.3 -> 14.9; 600^2 shallow water FP32 30.8 -> 19.2.
-bool step_in_tiles(const std::vector<LatticeDesc> &descs)
+bool step_in_tiles(const std::vector<LatticeDesc> &descs, int64_t cus)
 {
     int64_t cost = 0, line = kTileWavesSwe;
     bool any = false, one_d = false;
@@ -1809,7 +1809,7 @@ bool step_in_tiles(const std::vector<LatticeDesc> &descs)
         if (d.tile_rows == 0) return false;
         any = true;
         if (d.variant != V_SWE2) line = kTileWaves;
-        cost += tile_waves(d.nx, d.ny, d.tile_rows, num_cus()) + 8;
+        cost += tile_waves(d.nx, d.ny, d.tile_rows, cus) + 8;
     }
     return any && cost + (one_d ? 12 : 0) <= line + 8;
 }
@@ -1823,7 +1823,7 @@ int rebuild_table(arlbm_server *s)
         d.iter0 = r.iter0;
         descs.push_back(d);
     }
-    const bool tiles = step_in_tiles(descs);
+    const bool tiles = step_in_tiles(descs, num_cus());
     for (size_t i = 0; i < descs.size(); ++i) {
         s->resident[i].own = own_launch(descs[i]) || (tiles && descs[i].variant >= V_ADV2);
         if (!s->resident[i].own) lats.push_back(sched_lattice((int32_t)i, descs[i], s->precision == ARLBM_F64));
@@ -2487,6 +2487,31 @@ std::string plan_lattices(const arlbm_config *cfgs, int32_t n, std::vector<Sched
         lats.push_back(sched_lattice(i, d, cfgs[i].precision == ARLBM_F64));
     }
     return "";
+}
+
+extern "C" int arlbm_plan_tiles(const arlbm_config *cfgs, int32_t n, int32_t cus, int32_t *alone, int32_t *served)
+{
+    if (!cfgs || n < 0 || cus < 1 || (n > 0 && (!alone || !served)))
+        return sfail(nullptr, ARLBM_EINVAL, "bad argument");
+    std::vector<LatticeDesc> descs;
+    for (int32_t i = 0; i < n; ++i) {
+        const arlbm_config &c = cfgs[i];
+        std::string e = check_config(&c);
+        if (!e.empty()) return sfail(nullptr, ARLBM_EINVAL, e);
+        arlbm_sizes sz;
+        fill_sizes(&c, &sz);
+        LatticeDesc d{};
+        d.variant = variant_of(c.system, c.dim);
+        d.nx = (int32_t)c.nx;
+        d.ny = (int32_t)c.ny;
+        d.buf = c.dim == 2 && sz.f_bytes <= 0xffffffffull ? 1 : 0;
+        d.tile_rows = c.dim == 2 ? choose_tile_rows(&c, cus) : 0;
+        descs.push_back(d);
+        alone[i] = c.dim == 3 ? choose_tile_z(c.system, c.precision == ARLBM_F64, c.nx, c.ny, c.nz, cus) : d.tile_rows;
+    }
+    const bool tiles = step_in_tiles(descs, cus);
+    for (int32_t i = 0; i < n; ++i) served[i] = own_launch(descs[i]) || tiles ? alone[i] : 0;
+    return ARLBM_OK;
 }
 
 extern "C" int arlbm_plan_groups(const arlbm_config *cfgs, int32_t n, int32_t waves, int32_t *group_of,

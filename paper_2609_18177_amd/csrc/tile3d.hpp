@@ -30,19 +30,12 @@ namespace arlbm {
 // FP64 Euler 63 against 61; 1024 threads for 8 x 8 x 8: 64^3 39 against 32.)
 template <int SYS, typename T, bool kLow>
 struct Block3 {
-    static constexpr int TX = 8, TY = 8, TZ = kLow || (SYS == 3 && sizeof(T) == 8) ? 4 : 8;
+    static constexpr int TX = kTile3X, TY = kTile3Y, TZ = kLow ? 4 : tile3_z(SYS, sizeof(T) == 8);
     static constexpr int kCells = TX * TY * TZ, kThreads = 512;
     static constexpr int W3 = TX + 6, H3 = TY + 6, N3 = W3 * H3 * (TZ + 6);
     static constexpr int W2 = TX + 4, H2 = TY + 4, N2 = W2 * H2 * (TZ + 4);
     static constexpr int W1 = TX + 2, H1 = TY + 2, N1 = W1 * H1 * (TZ + 2);
 };
-// Tiles per CU up to which the tiles beat the march, whose workgroups take as
-// long for a small lattice as for one of their own size: Euler FP32 64^3 (2
-// tiles per CU) 32 against 81 us, 96^3 (6.75) 107 against 91, FP64 61 / 162
-// and 246 / 193; advection 96^3 25 / 31 and 128^3 (16) 50 / 51, FP64 39 / 46
-// and 78 / 80.
-constexpr int kTiles3PerCu = 5, kTiles3PerCuAdv = 16;
-
 template <int SYS, typename T, bool kLow>
 __global__ __launch_bounds__((Block3<SYS, T, kLow>::kThreads)) void k_tile3d(LatticeDesc L, int64_t iter, int32_t ntx,
                                                                         int32_t nty, int32_t nwork)
