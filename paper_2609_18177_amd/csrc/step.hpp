@@ -712,6 +712,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     auto first_cell = [&](int w) { return (int)((int64_t)w * nx / nw); };
     const int c0 = first_cell(gwave), c1 = first_cell(gwave + 1);
     const int64_t n0 = iter0 - L.iter0;
+    const DevScalars *sc = L.sc;
     const Phys<T> P = make_phys<T>(L);
     constexpr bool src = SYS == 2;
     const bool has_bed = src && L.bed != nullptr;
@@ -806,24 +807,21 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
 #pragma unroll
         for (int v = 0; v < V; ++v) db[v] = has_bed ? ddiv<T>(br[v] - bl[v], T(2) * P.dx) : T(0);
     }
-    MarchEntry at;
-    MarchGate *gate = nullptr;
-    if constexpr (GRID) {
-        unsigned long long *o = (unsigned long long *)L.u[0] + grid_march_words<SYS, T>(nblk);
-        at = *(const MarchEntry *)o;
-        gate = (MarchGate *)(o + kGateWord);
-    }
-    else at = {L.sc->t[n0 % 3], abar_of(L, (int)(n0 % 3), 0), L.sc->last_dt, L.sc->null_launches};
-    double t = at.t, t_before = t, last_dt = at.last_dt;
-    double ab = at.bound;
-    const unsigned long long null0 = at.null_launches;
+    const MarchEntry *entry = nullptr;
+    if constexpr (GRID) entry = (const MarchEntry *)((const unsigned long long *)L.u[0] + grid_march_words<SYS, T>(nblk));
+    double t = GRID ? entry->t : sc->t[n0 % 3], t_before = t, last_dt = GRID ? entry->last_dt : sc->last_dt;
+    double ab;
+    if constexpr (GRID) ab = entry->bound;
+    else ab = abar_of(L, (int)(n0 % 3), 0);
+    const unsigned long long null0 = GRID ? entry->null_launches : sc->null_launches;
     unsigned flags = 0;
     unsigned long long bad = ~0ull;
     Coefs<T> cf0;
     coefs_of<D, T>(L, ab, 0.0, 0.0, cf0);
     if constexpr (GRID) {  // nothing is written before this
         __shared__ int go;
-        if (threadIdx.x == 0) go = gather(gate, (unsigned)nblk, L.gather_looks);
+        if (threadIdx.x == 0)
+            go = gather((MarchGate *)((unsigned long long *)entry + kGateWord), (unsigned)nblk, L.gather_looks);
         __syncthreads();
         if (!go) return;
     }
@@ -1071,7 +1069,8 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
     __syncthreads();
     const int64_t ne = n0 + nsteps;
     T *fout = (T *)L.f[ne & 1];
-    const bool there = s == 0 && (nsteps & 1) == 0;  // in the buffer it was read from, and others may still read it
+    // (a state in the buffer it was read from, which other workgroups may still read, stays)
+    const bool there = GRID && s == 0 && (nsteps & 1) == 0;
 #pragma unroll
     for (int v = 0; v < V; ++v)
         if (own[v] && !there)
@@ -1079,7 +1078,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             for (int k = 0; k < Q; ++k)
 #pragma unroll
                 for (int c = 0; c < M; ++c) sto(fout + (size_t)(k * M + c) * L.pstride, (unsigned)x[v], f[v][k][c]);
-    unsigned any = flags & (4u | kStalled);
+    unsigned any = flags & (GRID ? 4u | kStalled : 4u);
     if (__ballot((flags & 1u) != 0u)) any |= 1u;
     if (__ballot((flags & 2u) != 0u)) any |= 2u;
     DevScalars *so = L.sc;
@@ -1092,7 +1091,7 @@ __global__ __launch_bounds__((GRID ? kGridWaves : kMarchWaves) * kWave) void k_m
             so->t[(ne + 2) % 3] = s == nsteps ? t_before : t;
             so->t[ne % 3] = t;
             so->last_dt = last_dt;
-            so->null_launches = null0 + (any & (4u | kStalled) ? 0ull : (unsigned long long)(nsteps - s));
+            so->null_launches = null0 + (any & (GRID ? 4u | kStalled : 4u) ? 0ull : (unsigned long long)(nsteps - s));
         }
         if (lane <= abar_mask(L)) {
             AbarCopy &cur = so->abar[ne % 3][lane], &nxt = so->abar[(ne + 1) % 3][lane];

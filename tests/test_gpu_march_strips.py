@@ -329,3 +329,24 @@ def test_both_sides_of_five_tiles_per_cu(system, nz):
     G.step(4)
     assert rel_l1(G.moments(), Lo.moments()) <= TOL3[system]
     G.close()
+
+
+def test_fp64_advection_beyond_4_gib():
+    """FP64 advection, two columns per lane, with population buffers beyond 4
+    GiB (64-bit addresses in place of buffer resources): a periodic lattice
+    and the same 26 x 26 times over take the same steps."""
+    require_gpu()
+    p = crop(W.advection_sine_2d(n=400, ax=0.8, ay=-0.5), 400, 400, bc=(P,) * 4)
+    k = 26
+    q = dataclasses.replace(p, nx=k * p.nx, ny=k * p.ny, x1=p.x0 + k * (p.x1 - p.x0), y1=p.y0 + k * (p.y1 - p.y0),
+                            U0=np.tile(p.U0, (1, k, k)))
+    assert A.query_sizes(A.config_from(q, precision=A.F64)).f_bytes > 1 << 32
+    say(f"[march, beyond 4 GiB] advection {q.nx}^2 FP64")
+    a, b = (gpu_lattice(x, A.F64) for x in (p, q))
+    a.step(3)
+    b.step(3)
+    assert a.sync() == b.sync()
+    U = b.moments()
+    b.close()
+    assert np.array_equal(np.tile(a.moments(), (1, k, k)), U)
+    a.close()
