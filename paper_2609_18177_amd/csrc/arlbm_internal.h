@@ -21,7 +21,7 @@ static_assert(strip_out_w(1) == kOutW && strip_out_w(2) == 120, "strip geometry"
 // kMarchWaves waves, of one cell per lane where 58 cells a wave hold the
 // lattice (Euler FP32 400 cells 1.67 against 1.70 us per step of two, 100 cells
 // 1.08 against 1.51), else, for advection, of two (1920 cells FP32 1.13 us,
-// FP64 1.72, against 1.92 and 2.07 over several workgroups).  Larger lattices
+// FP64 1.72, against 1.92 and 2.07 for 1921 over several workgroups).  Larger lattices
 // march over several workgroups: for Euler and shallow water beyond 928 cells
 // (928 in one against 929 in several: Euler FP32 2.46 against 2.58 us, FP64 3.78
 // against 3.22, shallow water 1.98 against 2.22 and 3.16 against 2.90; two cells

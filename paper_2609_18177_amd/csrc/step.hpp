@@ -572,9 +572,9 @@ __device__ __forceinline__ void seg1d(const LatticeDesc &L, int64_t iter, int c0
 // every SIMD has one wave (up to 232 cells), one CU's instruction issue above.
 // us per step, against the march that kept its populations in memory between
 // steps, and (above 928 cells) one launch per step: advection FP64 256 cells
-// 2.38 -> 0.78, Euler FP32 928 4.45 -> 2.66, FP64 6.61 -> 3.86, shallow water
-// FP64 600 4.81 -> 2.82, reactive FP64 256 7.84 -> 5.36; two cells per lane at
-// 1920 cells: advection FP32 4.06 -> 1.13.  GRID against one launch per step
+// 2.38 -> 0.78, Euler FP32 928 4.45 -> 2.46, FP64 6.61 -> 3.78, shallow water
+// FP64 600 4.81 -> 2.4, reactive FP64 256 7.84 -> 4.7; two cells per lane at
+// 1920 cells: advection FP32 4.06 -> 1.11.  GRID against one launch per step
 // (about 1 us of a step is the exchange): 4096 cells Euler FP32 4.54 -> 2.58,
 // FP64 5.11 -> 3.48, shallow water FP32 4.33 -> 2.55, reactive FP64 7.47 -> 6.09,
 // advection FP32 3.90 -> 1.88; 14800 cells Euler FP32 4.52 -> 2.69.
